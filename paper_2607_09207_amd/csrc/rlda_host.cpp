@@ -272,6 +272,7 @@ rlda_status run_impl(rl_decode_attn_t h, int32_t batch, int32_t num_pages, int32
   p.group = h->group;
   p.max_pages = c.max_pages_per_seq;
   p.nranges = ranges;
+  p.inv_ranges = c.num_work_ranges > 0 ? 0.f : 1.0f / (float)ranges;
   p.scale_log2 = h->scale * 1.4426950408889634f;
   p.out_bf16 = c.out_dtype == RLDA_BF16;
   memcpy(p.q_head, h->q_head, sizeof p.q_head);
@@ -519,6 +520,7 @@ rlda_status rl_decode_attn_run_multi(rl_decode_attn_t h, int32_t batch, int32_t 
     if (ranges > max_units) ranges = (int)max_units;
     if (ranges < 1) ranges = 1;
     p.nranges = ranges;
+    p.inv_ranges = c.num_work_ranges > 0 ? 0.f : 1.0f / (float)ranges;
     p.counters = (uint32_t*)(ws + wl.counters);
     p.call_tag = next_call_tag();
     p.part_ml = (float*)(ws + wl.part_ml);

@@ -10,7 +10,8 @@
 //      workgroup u owns the u-th of nranges equal-cost shares of it.  Long
 //      sequences are therefore cut across many workgroups and short ones packed
 //      together: every workgroup streams the same work however long the tail of
-//      the length distribution is (Sec. 2.3 on long-tail decode).
+//      the length distribution is (Sec. 2.3 on long-tail decode).  Small calls take
+//      whole segments instead, one per workgroup (see "How the list is cut").
 //   2. Page gather.  Each of the 4 waves of a workgroup takes a quarter of the
 //      share and walks it as one continuous stream of pages: its lanes decode 64
 //      positions at a time (sequence, KV head, page id, valid tokens, segment
@@ -103,6 +104,32 @@ __device__ __forceinline__ uint32_t word_of(u32x4 v, int i) { return v[i]; }
 __device__ __forceinline__ uint32_t word_of(u32x2 v, int i) { return v[i]; }
 __device__ __forceinline__ uint32_t word_of(uint32_t v, int) { return v; }
 
+// Inclusive sum and maximum (of non-negative values) over the lanes 0 .. l of a wave,
+// by DPP: shifts within rows of 16, then the rows' last lanes broadcast to the rows
+// after them.  Each step is two VALU instructions where a shuffle is an LDS round trip.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, true);
+}
+__device__ __forceinline__ int wave_scan(int x) {
+  x += dpp_or_zero<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8
+  x += dpp_or_zero<0x112, 0xf>(x);
+  x += dpp_or_zero<0x114, 0xf>(x);
+  x += dpp_or_zero<0x118, 0xf>(x);
+  x += dpp_or_zero<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  x += dpp_or_zero<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ int wave_scan_max(int x) {
+  x = max(x, dpp_or_zero<0x111, 0xf>(x));
+  x = max(x, dpp_or_zero<0x112, 0xf>(x));
+  x = max(x, dpp_or_zero<0x114, 0xf>(x));
+  x = max(x, dpp_or_zero<0x118, 0xf>(x));
+  x = max(x, dpp_or_zero<0x142, 0xa>(x));
+  x = max(x, dpp_or_zero<0x143, 0xc>(x));
+  return x;
+}
+
 // Max / sum over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48).
 __device__ __forceinline__ float group_max(float x) {
   x = fmaxf(x, __shfl_xor(x, 16));
@@ -116,6 +143,13 @@ __device__ __forceinline__ float group_sum(float x) {
 
 
 // ---------------------------------------------------------------- helpers
+
+// Index of block b < n such that each of the 8 XCDs (block b runs on XCD b % 8) gets a
+// contiguous run of the indices.  A bijection of [0, n).
+__device__ __forceinline__ int xcd_contiguous(int b, int n) {
+  const int x = b & 7;
+  return x * (n >> 3) + min(x, n & 7) + (b >> 3);
+}
 
 __device__ __forceinline__ int64_t owner_of(int64_t x, int W, int64_t C) {
   // Largest u with floor(u*C/W) <= x: the share holding cost x.
@@ -242,6 +276,7 @@ struct Mfma {
   static constexpr int EB = FP8 ? 1 : 2;             // bytes per KV element
   static constexpr int kEB = EB;
   static constexpr int kDepth = FP8 ? RLDA_MFMA_DEPTH_FP8 : RLDA_MFMA_DEPTH;
+  static constexpr bool kHalfPages = FP8 || D == 64;   // at most 4 KiB of K and V per page and KV head
   static constexpr int KL = FP8 ? D / 64 : D / 32;   // 16-byte K loads per lane
   static constexpr int VB = DT * EB;                 // V bytes per row per lane
   typedef typename RowLoad<VB>::type VRow;
@@ -560,6 +595,7 @@ struct Valu {
   static constexpr bool kFp8 = false;
   static constexpr int kEB = 4;
   static constexpr int kDepth = 2;
+  static constexpr bool kHalfPages = false;
   static constexpr int CW = D / 4;
   static constexpr int NL = CW / 4;
   struct Frag {
@@ -771,6 +807,95 @@ __device__ __forceinline__ StreamChunk fetch_chunk(const Params& p, const int32_
   return c;
 }
 
+// ---------------------------------------------------------------- whole segments
+
+// All nb > 0 pages of KV head g of sequence b by one workgroup (every thread calls
+// it): each wave streams a quarter of the pages, the four states meet in LDS and the
+// rows are written; no cut piece leaves the workgroup.  With one segment there are no
+// boundaries to look for: the ids come 64 at a time ahead of a loop that issues the
+// same loads for every page (past the last one with descriptors of no records), so a
+// wave waits for the page it consumes only and keeps kDepth pages in flight.  What
+// bounds it is latency: lengths, ids and the first page are three dependent round trips.
+template <class Pol>
+__device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int nb, int tail,
+                                              float (*sacc)[16][Pol::kD + 4], float (*sml)[16][2]) {
+  constexpr int D = Pol::kD, kDepth = Pol::kDepth;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const int j0 = nb * wave / kWaves, j1 = nb * (wave + 1) / kWaves;
+  const int32_t* bt = p.block_table + (int64_t)b * p.max_pages;
+  int pid = j0 < j1 ? bt[j0 + min(lane, j1 - j0 - 1)] : -1;
+  Pol st;
+  st.setup(p, lane, p.stride_slot);
+  typename Pol::QOp qo;
+  Pol::load_q(qo, p, b, g, lane, true);
+  st.begin(qo, p, b, g, lane);
+  for (int cb = j0; cb < j1; cb += kChunk) {
+    const int cn = min(kChunk, j1 - cb);
+    if (cb > j0) pid = bt[cb + min(lane, cn - 1)];
+    typename Pol::Frag fr[kDepth];
+    float skm[kDepth], svm[kDepth];
+    int sval[kDepth];
+    auto issue = [&](typename Pol::Frag& f, int& val, float& ks, float& vs, int k) {
+      int pk = -1;
+      if (k < cn) {
+        pk = __builtin_amdgcn_readlane(pid, k);
+        if ((unsigned)pk >= (unsigned)p.num_pages) {   // not a page of the pool: contributes nothing
+          if (lane == 0) atomicOr(p.flags, kFlagBadPage);
+          pk = -1;
+        }
+      }
+      val = pk < 0 ? 0 : (cb + k == nb - 1 ? tail : kPage);
+      const int64_t po = (pk >= 0) ? (int64_t)pk * p.stride_page + (int64_t)g * p.stride_head : 0;
+      const uint32_t nrec = val > 0 ? (uint32_t)((val - 1) * p.stride_slot + D * Pol::kEB) : 0u;
+      ks = 1.f;
+      vs = 1.f;
+      if constexpr (Pol::kFp8) {
+        const int64_t si = (pk >= 0) ? (int64_t)pk * p.num_kv_heads + g : 0;
+        const uint32_t sb = (pk >= 0) ? 4u : 0u;
+        ks = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.k_scale + si, sb), 0, 0, 0));
+        vs = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.v_scale + si, sb), 0, 0, 0));
+      }
+      st.issue(f, make_rsrc_uni((const char*)p.k + po, nrec), make_rsrc_uni((const char*)p.v + po, nrec));
+    };
+#pragma unroll
+    for (int k = 0; k < kDepth - 1; ++k) issue(fr[k], sval[k], skm[k], svm[k], k);
+    for (int i = 0; i < cn; i += kDepth) {
+#pragma unroll
+      for (int k = 0; k < kDepth; ++k) {
+        const int si = (k + kDepth - 1) % kDepth;
+        issue(fr[si], sval[si], skm[si], svm[si], i + k + kDepth - 1);
+        if (i + k < cn) st.compute(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
+      }
+    }
+  }
+  st.to_lds(sacc[wave], sml[wave], lane);
+  lds_barrier();
+  // The four states, weighted by their maxima: thread (row h, D/16 outputs).
+  constexpr int DPT = D / 16;
+  const int h = tid / 16, d0 = (tid % 16) * DPT;
+  if (h >= p.group) return;
+  float ms[kWaves], M = neg_inf(), Ls = 0.f, o[DPT];
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    ms[w] = sml[w][h][0];
+    M = fmaxf(M, ms[w]);
+  }
+#pragma unroll
+  for (int e = 0; e < DPT; ++e) o[e] = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const float a = ms[w] == neg_inf() ? 0.f : __builtin_amdgcn_exp2f(ms[w] - M);
+    Ls += a * sml[w][h][1];
+#pragma unroll
+    for (int c = 0; c < DPT; c += 4) {
+      const f32x4 v = *(const f32x4*)&sacc[w][h][d0 + c];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[c + e] += a * v[e];
+    }
+  }
+  store_out<D, DPT>(p, b, s_qhead[g * p.group + h], d0, o, Ls > 0.f ? 1.f / Ls : 0.f);
+}
+
 // ---------------------------------------------------------------- the kernel
 
 #ifndef RLDA_PROMPT_TEMPORAL
@@ -834,7 +959,7 @@ void decode_attention_kernel(const Params p) {
   // Non-empty units before each unit (the work split prices every segment's start).
   __shared__ uint16_t s_ne[kB + 1];
   __shared__ int32_t s_seg[2 * kWaves];
-  __shared__ int32_t s_scan[kWaves], s_scan_ne[kWaves];
+  __shared__ int32_t s_scan[kWaves], s_scan_ne[kWaves], s_scan_max[kWaves];
   __shared__ int32_t s_last[2];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -846,10 +971,7 @@ void decode_attention_kernel(const Params p) {
   // runs on XCD b % 8); each XCD gets a contiguous run of shares, so neighbouring
   // work (the sequences of a GRPO group reading the same prompt pages, the pieces
   // of one split segment) shares one L2.  A bijection of [0, W).
-  const int u = [&] {
-    const int b = blockIdx.x, x = b & 7, i = b >> 3, q = W >> 3, r = W & 7;
-    return x * q + min(x, r) + i;
-  }();
+  const int u = xcd_contiguous(blockIdx.x, W);
   const int batch = p.batch, Hkv = p.num_kv_heads, G = p.group;
   const int cap = p.max_pages * kPage;
   // Multi-token runs: nrc segments of 16 NT rows per (sequence, KV head), Hs per
@@ -903,18 +1025,11 @@ void decode_attention_kernel(const Params p) {
       atomicOr(p.flags, kFlagPrefixClamped);
     // Prefix sums of the packs' pages and of the non-empty packs, in pack order
     // (= lane order of the packs' first members).
-    int x = n, xn = n > 0;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o), yn = __shfl_up(xn, o);
-      if (lane >= o) {
-        x += y;
-        xn += yn;
-      }
-    }
+    const int x = wave_scan(n), xn = wave_scan(n > 0), xm = wave_scan_max(n);
     if (lane == 63) {
       s_scan[wave] = x;
       s_scan_ne[wave] = xn;
+      s_scan_max[wave] = xm;
     }
     if (tid < p.num_q_heads) s_qhead[tid] = qh0;
     if (tid < 2 * kWaves) s_seg[tid] = -1;
@@ -969,7 +1084,7 @@ void decode_attention_kernel(const Params p) {
     {
       const int per = (nunits + kThreads - 1) / kThreads;
       const int lo = min(tid * per, nunits), hi = min(lo + per, nunits);
-      int sum = 0, cnt = 0, bad = 0;   // pages, non-empty units
+      int sum = 0, cnt = 0, most = 0, bad = 0;   // pages, non-empty units, the largest unit
       for (int b = lo; b < hi; ++b) {
         if constexpr (PACK) {
           // Pack b: members b0 .. b0 + np - 1 of group i; the prompt once, then each member's own pages.
@@ -983,6 +1098,7 @@ void decode_attention_kernel(const Params p) {
           s_pre[b + 1] = n;
           sum += n;
           cnt += n > 0;
+          most = max(most, n);
           continue;
         }
         int L = p.seq_lens[b];
@@ -1013,20 +1129,14 @@ void decode_attention_kernel(const Params p) {
         s_tail[b] = (uint8_t)(L - (nfull - 1) * kPage);   // 1..16 when nfull > 0
         sum += n;
         cnt += n > 0;
+        most = max(most, n);
       }
       if (bad && u == 0) atomicOr(p.flags, kFlagBadLen);
-      int x = sum, xn = cnt;
-  #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o), yn = __shfl_up(xn, o);
-        if (lane >= o) {
-          x += y;
-          xn += yn;
-        }
-      }
+      const int x = wave_scan(sum), xn = wave_scan(cnt), xm = wave_scan_max(most);
       if (lane == 63) {
         s_scan[wave] = x;
         s_scan_ne[wave] = xn;
+        s_scan_max[wave] = xm;
       }
       if (tid < p.num_q_heads) s_qhead[tid] = qh0;
       if (tid < 2 * kWaves) s_seg[tid] = -1;
@@ -1093,19 +1203,73 @@ void decode_attention_kernel(const Params p) {
     }
   }
 
+  // How the list is cut.  Uniform over the grid; calibrate.work_split mirrors it.  A run
+  // with a forced share count (inv_ranges 0) always takes W equal shares.
+  //   Whole segments: each workgroup takes one segment.  That skips the share search and
+  // the hand-off of cut pieces (store, count, read back), about 5 us together, and its
+  // waves stream (nbmax - fair) / 4 pages more than under equal shares of `fair` pages,
+  // 0.4 to 0.6 us each while so few of them run.  us a call on batches of equal lengths,
+  // equal shares against whole segments, 16 / 32 / 64 / 112 pages:
+  //   28/4 bf16 d 128, B = 4:   13.2 / 13.9 / 14.6 / 15.4   against  8.1 / 9.7 / 15.8 / 26.7
+  //                    B = 16:  11.2 / 12.4 / 14.3 / 17.5            8.2 / 10.3 / 17.7 / 28.7
+  //                    B = 32:  12.3 / 14.3 / 18.7 / 25.9            8.4 / 11.7 / 19.7 / 31.5
+  //   40/8 fp8 d 128,  B = 4:   14.2 / 14.5 / 14.9 / 15.5            7.4 / 9.5 / 14.3 / 21.5
+  //                    B = 32:  12.9 / 15.1 / 20.0 / 27.5            7.7 / 10.0 / 15.0 / 22.4
+  //   64/8 bf16 d 64,  B = 16:  10.9 / 12.3 / 14.4 / 17.7            6.5 / 8.2 / 12.2 / 18.3
+  // (28/4, B = 60, 200 pages: 68.6 against 62.3).  `over` is where the two meet, in pages
+  // over an equal share, by segments per workgroup: with one workgroup per CU whole
+  // segments leave CUs idle that could read, with two (half-size pages) they don't until
+  // half the workgroups are gone.  Multi-token, packed and prompt-state runs stream whole
+  // segments through the general loop, which is slower a page.
+  //   Equal shares hold at least 4 pages (one a wave), and so many that the largest
+  // segment falls into about 16 pieces, one batch of its final merge; of longer segments
+  // at least sqrt(1.25 nbmax), where pages and pieces cost alike (a share's page 0.15 us,
+  // a piece 0.19 us).  12/2 heads, one sequence of 112 pages: 31.3 us in 256 shares, 13.5
+  // so.  Where that bound holds the shares are a multiple of the segments, so that equal
+  // segments are cut alike.
+  const int nseg = nunits * Hs;
+  int W2 = W;   // equal shares used
+  bool direct = false;
+  if (p.inv_ranges > 0.f) {
+    int nbm = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) nbm = max(nbm, s_scan_max[w]);
+    const float nb = (float)nbm, fair = (float)(int)C * p.inv_ranges, segs = (float)nseg * p.inv_ranges;
+    const float over = (MULTI || PROMPT)  ? fmaxf(40.f - 48.f * segs, 20.f)
+                       : !Pol::kHalfPages ? fmaxf(54.f - 72.f * segs, 26.f)
+                                          : (D == 64 ? 78.f : 57.f) + fmaxf(80.f * segs - 20.f, 0.f);
+    direct = uni(segs <= 1.f && nb - fair <= over) != 0;
+    const float least = fmaxf(fminf(0.0625f * nb - 1.f, __builtin_amdgcn_sqrtf(1.25f * nb)), 4.f);
+    if (fair < least)
+      W2 = uni(min(W, nseg * (int)__builtin_ceilf((float)(int)C * __builtin_amdgcn_rcpf((float)nseg * least))));
+  }
   // Never more shares than positions (C >= T >= Wn).  A share can still hold no
   // position when the shares are shorter than two costs.
-  const int Wn = (int)min((int64_t)W, T);
-  if (u >= Wn) return;
+  const int Wn = (int)min((int64_t)W2, T);
+  if (direct ? (int)blockIdx.x >= nseg : u >= Wn) return;
 
   // 3. This workgroup's share [r0, r1) of the flattened (sequence, KV head, page)
-  //    list, and this wave's quarter [w0, w1) of it: equal parts of the cost
-  //    [floor(u C / Wn), floor((u + 1) C / Wn)), each taken as the positions whose
-  //    cost falls inside it.  Each wave walks its own pieces without waiting for
-  //    the others; a piece inside its quarter is written directly.
+  //    list, and this wave's quarter [w0, w1) of it.  Each wave walks its own pieces
+  //    without waiting for the others; a piece inside its quarter is written directly.
   int w0, w1, wunit = 0;   // wunit: the unit of position w0 (when w0 < T)
   int64_t r0, r1;
-  {
+  if (direct) {
+    // One segment, in page quarters.  Blocks 0 .. nseg - 1 work (every XCD has its
+    // part of them), contiguous runs of segments on one XCD as for the shares.
+    const int sg = xcd_contiguous(blockIdx.x, nseg);
+    wunit = sg / Hs;
+    const int gv = sg - wunit * Hs, pre = uni(s_pre[wunit]), nb = uni(s_pre[wunit + 1]) - pre;
+    if constexpr (!MULTI && !PROMPT) {
+      if (nb > 0) whole_segment<Pol>(p, wunit, gv, nb, uni(s_tail[wunit]), s_acc, s_ml);
+      return;
+    }
+    r0 = Hs * pre + gv * nb;
+    r1 = r0 + nb;
+    w0 = (int)r0 + nb * wave / kWaves;
+    w1 = (int)r0 + nb * (wave + 1) / kWaves;
+  } else {
+    // Equal parts of the cost [floor(u C / Wn), floor((u + 1) C / Wn)), each taken as
+    // the positions whose cost falls inside it.
     // Lane i < 5 turns quarter boundary i into the first position of cost at least
     // that boundary: the unit holding it (K(b) <= B < K(b + 1)), then the segment
     // and the page within it (the segment's start cost maps to its first page).

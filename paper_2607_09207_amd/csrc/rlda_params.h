@@ -67,6 +67,7 @@ struct Params {
   int32_t group;               // G = Hq / Hkv
   int32_t max_pages;           // block-table row length
   int32_t nranges;             // workgroups = equal-cost shares of the flattened work
+  float inv_ranges;            // 1 / nranges, or 0: the caller fixed the share count (equal shares always)
   float scale_log2;            // softmax scale * log2(e)
   int32_t out_bf16;            // 0: fp32 output, 1: bf16 output
   // Shared-prompt (grouped) runs; all null / 0 otherwise.

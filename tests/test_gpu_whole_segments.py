@@ -1,0 +1,70 @@
+"""The decode kernel's choice of shares, at the sizes where it can go wrong.
+
+Without a forced share count the kernel gives each workgroup one whole (sequence, KV
+head) segment when there is a workgroup for each and none is much longer than an equal
+share, and otherwise cuts the list into equal shares, fewer of them when segments would
+fall into many pieces.  The lengths below put calls on each side: fewer pages than waves,
+last pages of 1 and 16 tokens, more than 64 pages per wave (a second chunk of page ids),
+as many segments as workgroups and one more, a long segment among short ones, one
+segment alone.  Every output is compared with the fp64 oracle; the multi-token and the
+packed grouped call take the same choice.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2607_09207_amd import inputs as I
+from test_gpu_grouped import run_grouped
+from test_gpu_multi import run_multi
+from test_gpu_parity import TOL, assert_close, gpu_run, torch_cuda  # noqa: F401  (the fixture)
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # pages per segment below, at and above the four waves; empty sequences between
+    "few_pages_bf16": ("bf16", 28, 4, 128, [1, 16, 17, 0, 33, 48, 64, 65, 80, 0, 128]),
+    "few_pages_fp8": ("fp8_e4m3fn", 40, 8, 128, [1, 16, 17, 0, 64, 65, 81]),
+    "few_pages_d64": ("bf16", 16, 16, 64, [1, 15, 49, 256, 0, 257]),
+    "few_pages_f32": ("f32", 4, 2, 64, [1, 16, 17, 0, 64, 65, 250]),
+    # every workgroup has a segment (256 of them), and one sequence more than that
+    "all_workgroups_bf16": ("bf16", 8, 8, 64, [40 + 7 * i for i in range(64)]),
+    "more_segments_than_workgroups": ("bf16", 16, 16, 128, [20 + 3 * i for i in range(17)]),
+    # more than 64 pages to a wave: equal long segments on three quarters of the workgroups
+    "second_id_chunk_fp8": ("fp8_e4m3fn", 16, 16, 64, [4170 - i for i in range(24)]),
+    # a long segment among short ones, and one or two segments alone (equal shares,
+    # fewer than workgroups, many pieces)
+    "one_long": ("bf16", 12, 2, 128, [9000, 5, 17, 300]),
+    "alone_bf16": ("bf16", 8, 1, 128, [3001]),
+    "alone_fp8": ("fp8_e4m3fn", 4, 2, 64, [12345]),
+    "alone_f32": ("f32", 1, 1, 128, [2049]),
+}
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_default_shares_match_the_oracle(torch_cuda, name, out):
+    kv, Hq, Hkv, d, lens = CASES[name]
+    if kv == "f32" and out == "bf16":
+        pytest.skip("fp32 caches have fp32 outputs")
+    w = I.make_custom(lens, Hq, Hkv, d, q_dtype="f32" if kv == "f32" else "bf16", kv_dtype=kv, seed=71, extra_pages=2)
+    got, flags = gpu_run(torch_cuda, w, out_dtype=out, tag=f"shares {name}")
+    assert flags == 0
+    assert_close(got, oracle.run(w), kv, f"shares {name} out={out}")
+
+
+@pytest.mark.parametrize("kv,d,G", [("bf16", 128, 7), ("bf16", 64, 4), ("fp8_e4m3fn", 128, 5)])
+def test_default_shares_of_multi_token_rows(torch_cuda, kv, d, G):
+    lens = [5, 16, 17, 200, 64, 333, 1]
+    w = I.make_multi(lens, [min(L, 4) for L in lens], 2 * G, 2, d, kv_dtype=kv, seed=72, extra_pages=1)
+    got, flags = run_multi(torch_cuda, w, max_q_len=4)
+    assert flags == 0
+    assert np.max(np.abs(got - oracle.run_multi(w))) <= TOL[kv]
+
+
+@pytest.mark.parametrize("prompt", [32, 512])
+def test_default_shares_of_packed_groups(torch_cuda, prompt):
+    tails = [1, 16, 17, 40, 0, 300, 33, 5]
+    w = I.make_custom([prompt + t for t in tails], 12, 2, 128, seed=73, shared_prefix=(4, prompt), extra_pages=1)
+    got, flags = run_grouped(torch_cuda, w, 4, [prompt // 16] * 2)
+    assert flags == 0
+    assert_close(got, oracle.run(w), "bf16", f"packed prompt={prompt}")
