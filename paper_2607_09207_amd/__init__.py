@@ -81,6 +81,11 @@ class DecodeAttention:
                    "rl_decode_attn_grouped_workspace_size")
         self.grouped_workspace_bytes = int(n.value)
         self._ws = {}
+        # The native call path (csrc/fastcall.cpp); it shares the workspaces by device.
+        self._fast = _abi.fastcall().Layer(h.value, self._ws, (num_q_heads, num_kv_heads, head_dim, page_size, max_batch,
+                                                               max_pages_per_seq),
+                                           (cfg.q_dtype, cfg.kv_dtype, cfg.out_dtype), self._kv_strides,
+                                           self.workspace_bytes + 256, self.grouped_workspace_bytes + 256)
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -100,7 +105,16 @@ class DecodeAttention:
             self._ws[key] = ws
         return ws
 
+    @staticmethod
+    def _answer(got, what: str):
+        """The native call path's answer: the output tensor, or a status to raise."""
+        if type(got) is int:
+            _abi.check(got, what)
+        return got
+
     # ---------------------------------------------------------------- argument checks
+    # Each method first offers the call to the native path, which takes it when all of
+    # these checks would pass; they decide, and report, the calls it leaves.
     # The kernels index the tensors by the handle's configuration; a tensor of the
     # wrong device, dtype, shape or layout is rejected here, before any launch.
 
@@ -190,6 +204,14 @@ class DecodeAttention:
         group's prompt pages (rl_decode_attn_run_grouped); prompt_pages_hint (host value,
         e.g. the largest prefix_pages entry, <= 0 unknown) picks its packed or
         prompt-pass form."""
+        if events is None:
+            fast = (q, k_cache, v_cache, block_table, seq_lens, k_scale, v_scale, stream, num_pages, out, workspace)
+            if group_size is None:
+                got = self._fast.run(*fast)
+            else:
+                got = self._fast.grouped(*fast, group_size, prefix_pages, prompt_pages_hint)
+            if got is not None:
+                return self._answer(got, "rl_decode_attn_run" if group_size is None else "rl_decode_attn_run_grouped")
         torch = _torch()
         B = int(q.shape[0])
         cfg = self.config
@@ -236,6 +258,10 @@ class DecodeAttention:
         workspace: its flags, segment counters and partials live in the library's static
         device array (limits: batch * Hkv <= 65536, head_dim <= 128).  `flags`: None, or
         a one-element int32 device tensor that receives the contract bits (OR-ed in)."""
+        got = self._fast.noalloc(q, k_cache, v_cache, block_table, seq_lens, k_scale, v_scale, stream, num_pages, out,
+                                 flags)
+        if got is not None:
+            return self._answer(got, "rl_decode_attn_run_noalloc")
         torch = _torch()
         B = int(q.shape[0])
         cfg = self.config
@@ -269,6 +295,11 @@ class DecodeAttention:
         are its last tokens and attend causally.  max_q_len (host value) bounds the
         rows per sequence; with max_q_len <= 16 and max_q_len * G <= 64 the decode
         kernel's page stream runs the call.  Returns out [total_q][Hq][d]."""
+        if events is None:
+            got = self._fast.multi(q, k_cache, v_cache, block_table, seq_lens, k_scale, v_scale, stream, num_pages, out,
+                                   workspace, q_start, max_q_len)
+            if got is not None:
+                return self._answer(got, "rl_decode_attn_run_multi")
         torch = _torch()
         total = int(q.shape[0])
         B = int(q_start.shape[0]) - 1
@@ -306,6 +337,10 @@ class DecodeAttention:
         """Write one decode step's K/V rows ([B][Hkv][d], the q dtype) into the caches at
         token seq_lens[b] - 1 of every sequence (rl_decode_attn_append); fp8 caches also
         update their per-page scales."""
+        got = self._fast.append(k_new, k_cache, v_cache, block_table, seq_lens, k_scale, v_scale, stream, num_pages,
+                                v_new, workspace)
+        if got is not None:
+            return _abi.check(got, "rl_decode_attn_append")
         torch = _torch()
         B = int(k_new.shape[0])
         cfg = self.config

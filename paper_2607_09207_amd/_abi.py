@@ -83,6 +83,30 @@ def load() -> ctypes.CDLL:
     return _lib
 
 
+_fast = None
+
+
+def fastcall():
+    """The native call path (csrc/fastcall.cpp), bound to the loaded library; raises if it
+    has not been built."""
+    global _fast
+    lib = load()
+    if _fast is None or _fast[0] is not lib:
+        import torch
+        try:
+            from . import _fastcall
+        except ImportError as e:
+            raise ImportError("the native call path is missing or does not load: build it with "
+                              f"__graft_entry__.build() or python -m paper_2607_09207_amd.build ({e})") from e
+        # CPU-only torch builds have no stream lookup; every call is then left to Python.
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        addr = [ctypes.cast(getattr(lib, "rl_decode_attn_" + n), ctypes.c_void_p).value
+                for n in ("run", "run_grouped", "run_multi", "run_noalloc", "append")]
+        _fastcall.bind(raw, *addr)
+        _fast = (lib, _fastcall)
+    return _fast[1]
+
+
 def check(status: int, what: str) -> None:
     if status != 0:
         raise RldaError(status, what)

@@ -17,6 +17,11 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 PROBE_SOURCES = [os.path.join(CSRC, "hbm_probe.hip")]
 PROBE_LIB = os.path.join(HERE, "libhbm_probe.so")
 
+# The Python binding's native call path (host code: the C++ compiler against torch).
+FASTCALL_SOURCE = os.path.join(CSRC, "fastcall.cpp")
+FASTCALL_LIB = os.path.join(HERE, "_fastcall.so")
+CXX = os.environ.get("CXX", "g++")
+
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed fp32 VALU forms are kept out of the generated code
@@ -50,13 +55,40 @@ def device_asm(out_path: str, source: int = 0) -> str:
     return out_path
 
 
+def build_fastcall(verbose: bool = False) -> str:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ext
+    tmp = FASTCALL_LIB + ".tmp%d" % os.getpid()
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE]
+    for d in ext.include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    cmd += [FASTCALL_SOURCE, "-o", tmp, "-L", ext.TORCH_LIB_PATH, "-Wl,-rpath," + ext.TORCH_LIB_PATH,
+            "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building the native call path failed:\n" + r.stdout + r.stderr)
+    os.replace(tmp, FASTCALL_LIB)
+    return FASTCALL_LIB
+
+
 def build_all(verbose: bool = False) -> None:
-    """The attention library and the read-bandwidth probe library."""
-    build(verbose=verbose)
-    build(verbose=verbose, out=PROBE_LIB, sources=PROBE_SOURCES)
+    """The attention library, the read-bandwidth probe library and the native call path
+    (three compilers at a time)."""
+    from concurrent.futures import ThreadPoolExecutor
+    with ThreadPoolExecutor(3) as pool:
+        jobs = [pool.submit(build, verbose), pool.submit(build, verbose, PROBE_LIB, (), PROBE_SOURCES),
+                pool.submit(build_fastcall, verbose)]
+        for j in jobs:
+            j.result()
 
 
 if __name__ == "__main__":
     build_all(verbose="-v" in sys.argv)
     print(LIB)
     print(PROBE_LIB)
+    print(FASTCALL_LIB)
