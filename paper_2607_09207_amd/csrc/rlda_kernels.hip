@@ -130,17 +130,31 @@ __device__ __forceinline__ int wave_scan_max(int x) {
   return x;
 }
 
-// Max / sum over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48).
+// Max / sum over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48), by
+// lane swaps: permlane16_swap of x with itself leaves the even rows of 16 (each in both
+// rows of its pair) in one result and the odd rows in the other, permlane32_swap the
+// halves.  Two VALU instructions a step; the LDS shuffles they replaced cost two round
+// trips on the score chain of every page and tile.
+__device__ __forceinline__ u32x2 swap16(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return u32x2{r[0], r[1]};
+}
+__device__ __forceinline__ u32x2 swap32(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return u32x2{r[0], r[1]};
+}
 __device__ __forceinline__ float group_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
+  const u32x2 a = swap16(x);
+  x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const u32x2 b = swap32(x);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 __device__ __forceinline__ float group_sum(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
+  const u32x2 a = swap16(x);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const u32x2 b = swap32(x);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
-
-
 
 // ---------------------------------------------------------------- helpers
 
