@@ -244,3 +244,13 @@ def test_packed_groups_at_one_sequence_per_thread(torch_cuda):
     got, flags = run_grouped(torch_cuda, w, 16, [3] * 16, ranges=61, tag="256 sequences, groups of 16")
     assert flags == 0
     assert_close(got, oracle.run(w), "bf16", "groups of 16, batch 256")
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3fn"])
+@pytest.mark.parametrize("members", [1, 2, 3, 4, 5])
+def test_prompt_pass_at_every_tile_count(torch_cuda, kv, members):
+    """G = 16 rows a member: 1 to 4 tiles of a job in use, and a fifth member in a second job."""
+    w = grouped_case(16, 1, 64, members, 176, [0, 1, 40, 16, 333][:members], kv=kv, seed=80 + members)
+    got, flags = run_grouped(torch_cuda, w, members, [11], tag=f"tiles members={members}")
+    assert flags == 0
+    assert_close(got, oracle.run(w), kv, f"prompt tiles members={members}")
