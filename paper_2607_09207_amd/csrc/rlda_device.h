@@ -37,6 +37,32 @@ __device__ __forceinline__ int64_t uni64(int64_t x) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// Inclusive sum and maximum (of non-negative values) over the lanes 0 .. l of a wave,
+// by DPP: shifts within rows of 16, then the rows' last lanes broadcast to the rows
+// after them.  Each step is two VALU instructions where a shuffle is an LDS round trip.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, true);
+}
+__device__ __forceinline__ int wave_scan(int x) {
+  x += dpp_or_zero<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8
+  x += dpp_or_zero<0x112, 0xf>(x);
+  x += dpp_or_zero<0x114, 0xf>(x);
+  x += dpp_or_zero<0x118, 0xf>(x);
+  x += dpp_or_zero<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+  x += dpp_or_zero<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ int wave_scan_max(int x) {
+  x = max(x, dpp_or_zero<0x111, 0xf>(x));
+  x = max(x, dpp_or_zero<0x112, 0xf>(x));
+  x = max(x, dpp_or_zero<0x114, 0xf>(x));
+  x = max(x, dpp_or_zero<0x118, 0xf>(x));
+  x = max(x, dpp_or_zero<0x142, 0xa>(x));
+  x = max(x, dpp_or_zero<0x143, 0xc>(x));
+  return x;
+}
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, (int)kRsrcWord3);
 }

@@ -106,32 +106,6 @@ __device__ __forceinline__ uint32_t word_of(u32x4 v, int i) { return v[i]; }
 __device__ __forceinline__ uint32_t word_of(u32x2 v, int i) { return v[i]; }
 __device__ __forceinline__ uint32_t word_of(uint32_t v, int) { return v; }
 
-// Inclusive sum and maximum (of non-negative values) over the lanes 0 .. l of a wave,
-// by DPP: shifts within rows of 16, then the rows' last lanes broadcast to the rows
-// after them.  Each step is two VALU instructions where a shuffle is an LDS round trip.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_or_zero(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, true);
-}
-__device__ __forceinline__ int wave_scan(int x) {
-  x += dpp_or_zero<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8
-  x += dpp_or_zero<0x112, 0xf>(x);
-  x += dpp_or_zero<0x114, 0xf>(x);
-  x += dpp_or_zero<0x118, 0xf>(x);
-  x += dpp_or_zero<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
-  x += dpp_or_zero<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
-  return x;
-}
-__device__ __forceinline__ int wave_scan_max(int x) {
-  x = max(x, dpp_or_zero<0x111, 0xf>(x));
-  x = max(x, dpp_or_zero<0x112, 0xf>(x));
-  x = max(x, dpp_or_zero<0x114, 0xf>(x));
-  x = max(x, dpp_or_zero<0x118, 0xf>(x));
-  x = max(x, dpp_or_zero<0x142, 0xa>(x));
-  x = max(x, dpp_or_zero<0x143, 0xc>(x));
-  return x;
-}
-
 // Max / sum over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48), by
 // lane swaps: permlane16_swap of x with itself leaves the even rows of 16 (each in both
 // rows of its pair) in one result and the odd rows in the other, permlane32_swap the

@@ -131,61 +131,73 @@ void multi_query_kernel(const Params p) {
   __shared__ int32_t s_bad[S::NBUF][2 * kKH];   // page of the block not in the pool (contributes nothing)
   __shared__ int32_t s_scan[kWaves], s_emax[kWaves];
   __shared__ int16_t s_qh[kMaxQHeads];
-  __shared__ uint8_t s_cls[64];   // sequence classes (XCD placement, batches of at most 64)
-  // Per sequence: {L - n_b (position of query token 0), n_b G rows} (rows 0 when
-  // its offsets are inconsistent).
+  // Batches above 64, per sequence: {L - n_b (position of query token 0), n_b} (n_b 0
+  // when its offsets are inconsistent), and its ordering key.
   extern __shared__ int2 s_sq[];   // [batch], then s_key [batch]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int batch = p.batch, Hkv = p.num_kv_heads, G = p.group, Hq = p.num_q_heads;
   const int cap = p.max_pages * kPage;
-  // Ordering key of each sequence's row blocks: its key count L when they are
-  // dispatched together, -1 when each row block is ordered by its own key count.
   int32_t* s_key = (int32_t*)(s_sq + batch);
 
-  // 1. Rows of every sequence and the number of row blocks (identical in every
-  //    workgroup).  Inconsistent offsets give a sequence no rows; they, and lengths
-  //    out of range or shorter than the rows, raise the flag.
-  int nitems = 0, emax = 0;   // emax: the most keys any sequence's rows see
+  // 1. Rows of every sequence and the number of row blocks (identical in every wave).
+  //    Inconsistent offsets give a sequence no rows; they, and lengths out of range or
+  //    shorter than the rows, raise the flag.  Lane l holds sequence l: up to 64
+  //    sequences every wave reads for itself, without a barrier; above that they meet
+  //    in LDS.  An item's search, below, costs every workgroup the same again, so the
+  //    reductions go through DPP and the search takes three points a step: with LDS
+  //    shuffles and a binary search over all lengths the call on one or two short
+  //    sequences took 9.2 to 11.5 us, and 7.1 to 8.8 so; whole prompts (32 x 512 tokens,
+  //    12/2 heads) 58.2 and 53.5 us; chunks of long sequences 1420 and 1390 us.
+  int2 sq0 = make_int2(0, 0);   // the sequence of this lane: {L - n_b, n_b}
+  int key0 = -1;                // its ordering key (below)
+  int nitems = 0, emax = 0;     // row blocks; the most keys any sequence's rows see
   {
     int sum = 0, bad = 0, lmax = 0;
-    for (int b = tid; b < batch; b += kThreads) {
+    const bool many = batch > 64;
+    for (int b = many ? tid : lane; b < batch; b += kThreads) {
       const int q0 = p.q_start[b], q1 = p.q_start[b + 1];
       const bool ok = q0 >= 0 && q1 >= q0 && q1 <= p.total_q;
-      const int n = ok ? q1 - q0 : 0;
+      const int n = ok ? q1 - q0 : 0;   // n G < 2^24: q is addressed with 31-bit offsets
       int L = p.seq_lens[b];
       if (!ok || L < 0 || L > cap || n > L) bad = 1;
       L = min(max(L, 0), cap);
-      const int rows = (int)min((int64_t)n * G, (int64_t)INT32_MAX - kMultiRows);
-      s_sq[b] = make_int2(L - n, rows);
-      sum += (rows + kMultiRows - 1) / kMultiRows;
-      if (rows > 0) lmax = max(lmax, L);
+      sq0 = make_int2(L - n, n);
+      if (many) s_sq[b] = sq0;
+      sum += (n * G + kMultiRows - 1) / kMultiRows;
+      if (n > 0) lmax = max(lmax, L);
     }
     if (__builtin_amdgcn_ballot_w64(bad) != 0 && blockIdx.x == 0 && lane == 0) atomicOr(p.flags, kFlagBadLen);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      sum += __shfl_xor(sum, o);
-      lmax = max(lmax, __shfl_xor(lmax, o));
-    }
-    if (lane == 0) {
-      s_scan[wave] = sum;
-      s_emax[wave] = lmax;
-    }
+    sum = __builtin_amdgcn_readlane(wave_scan(sum), 63);
+    lmax = __builtin_amdgcn_readlane(wave_scan_max(lmax), 63);
     for (int e = tid; e < Hq; e += kThreads) s_qh[e] = p.q_head[e];
-    __syncthreads();
+    // Ordering key of each sequence's row blocks.  A sequence whose rows see at most an
+    // eighth of the largest job's keys apart is dispatched as a group (its row blocks
+    // then read its pages together): its key count L; -1: each row block is ordered by
+    // its own key count.
+    auto key_of = [&](int2 sq) { return sq.y > 0 && 8 * (int64_t)sq.y <= emax ? max(0, sq.x + sq.y) : -1; };
+    if (!many) {
+      nitems = sum;
+      emax = lmax;
+      key0 = key_of(sq0);
+      lds_barrier();   // s_qh
+    } else {
+      if (lane == 0) {
+        s_scan[wave] = sum;
+        s_emax[wave] = lmax;
+      }
+      lds_barrier();
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      nitems += s_scan[w];
-      emax = max(emax, s_emax[w]);
+      for (int w = 0; w < kWaves; ++w) {
+        nitems += s_scan[w];
+        emax = max(emax, s_emax[w]);
+      }
+      emax = uni(emax);
+      for (int b = tid; b < batch; b += kThreads) s_key[b] = key_of(s_sq[b]);
+      lds_barrier();
+      sq0 = s_sq[lane];
+      key0 = s_key[lane];
     }
-    // A sequence whose rows see at most an eighth of the largest job's keys apart
-    // is dispatched as a group (its row blocks then read its pages together).
-    for (int b = tid; b < batch; b += kThreads) {
-      const int2 sq = s_sq[b];
-      const int n = sq.y / G;
-      s_key[b] = (sq.y > 0 && 8 * (int64_t)n <= emax) ? max(0, sq.x + n) : -1;
-    }
-    __syncthreads();
   }
   const int64_t items = (int64_t)nitems * Hkv;
   if (blockIdx.x == 0 && tid == 0 && items > (int64_t)gridDim.x) atomicOr(p.flags, kFlagBadLen);
@@ -209,82 +221,85 @@ void multi_query_kernel(const Params p) {
   //    fill longest-job-first.  The row blocks of a sequence whose rows span at most
   //    an eighth of the largest job's keys all take the sequence's key count L: they
   //    run together and read the sequence's pages side by side, once from HBM; block t of the XCD takes item t of its set (blocks
-  //    past the set's end return).  Item t is found by a binary search on the key count: with
-  //    C(x) the items having at least x keys (a closed form per sequence, summed
-  //    across the wave), its key count x* is the largest x with C(x) > t.  Every wave
-  //    finds it (no barrier).
+  //    past the set's end return).  Item t is found by a search on the key count, three
+  //    points a step: with C(x) the items having at least x keys (a closed form per
+  //    sequence, summed across the wave), its key count x* is the largest x with C(x) > t.
+  //    Every wave finds it (no barrier).
   const int u = blockIdx.x, xcd = u & 7;
   const bool by_head = Hkv % 8 == 0, by_class = Hkv == 4;
   const int ncls = by_class ? 8 / Hkv : 1, my_cls = by_class ? xcd / Hkv : 0;
   const int hx = by_head ? Hkv / 8 : (by_class ? 1 : Hkv);   // KV heads per (b, rb) in the set
   const int t_first = (by_head || by_class) ? u >> 3 : u;
+  bool mine = true;   // batches of at most 64: this lane's sequence is in the set
   if (by_class && batch <= 64) {
-    // Class of each sequence: sort by estimated keys (descending; bitonic across the
-    // lanes of wave 0), then deal the ranks out in snake order 0, 1, .., K-1, K-1, .., 0.
-    if (wave == 0) {
-      float key = -1.f;
-      int id = lane;
-      if (lane < batch) {
-        const int2 sq = s_sq[lane];
-        const int nrb = (sq.y + kMultiRows - 1) / kMultiRows;
-        key = (float)nrb * ((float)max(sq.x, 0) + 0.5f * (float)(sq.y / G) + 1.f);
-      }
-#pragma unroll
-      for (int k = 2; k <= 64; k <<= 1)
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) {
-          const float ok = __shfl_xor(key, j);
-          const int oid = __shfl_xor(id, j);
-          const bool mine_first = key > ok || (key == ok && id < oid);
-          const bool keep = (((lane & j) == 0) == ((lane & k) == 0)) ? mine_first : !mine_first;
-          if (!keep) {
-            key = ok;
-            id = oid;
-          }
-        }
-      const int rr = lane % (2 * ncls);
-      if (id < batch) s_cls[id] = (uint8_t)(rr < ncls ? rr : 2 * ncls - 1 - rr);
+    // Class of each sequence: its rank by estimated keys (descending, ties by sequence;
+    // the keys compare as integers, being positive floats), the ranks dealt out in
+    // snake order 0, 1, .., K-1, K-1, .., 0.
+    const int nrb = (sq0.y * G + kMultiRows - 1) / kMultiRows;
+    const int key = __float_as_int((float)nrb * ((float)max(sq0.x, 0) + 0.5f * (float)sq0.y + 1.f));
+    int rank = 0;
+    for (int j = 0; j < batch; ++j) {
+      const int kj = __builtin_amdgcn_readlane(key, j);
+      rank += kj > key || (kj == key && j < lane);
     }
-    __syncthreads();
+    const int rr = rank % (2 * ncls);
+    mine = (rr < ncls ? rr : 2 * ncls - 1 - rr) == my_cls;
   }
-  auto in_set = [&](int b) {
-    return !by_class || (batch <= 64 ? (int)s_cls[b] : b % ncls) == my_cls;
-  };
-  // Row blocks of sequence `sq` with at least x keys (E is non-decreasing in rb).
+  // Row blocks of sequence `sq` with at least x >= 1 keys (E is non-decreasing in rb).
   auto at_least = [&](int2 sq, int key, int x) -> int {
-    const int rows = sq.y;
-    const int nrb = (rows + kMultiRows - 1) / kMultiRows;
-    if (x <= 0) return nrb;
+    const int nrb = (sq.y * G + kMultiRows - 1) / kMultiRows;
     if (key >= 0) return key >= x ? nrb : 0;   // dispatched as a group
-    const int64_t k = (int64_t)x - sq.x - 1;   // x >= 1: E >= x iff (r1 - 1) / G >= k
-    if (k <= 0) return nrb;
-    const int64_t thr = (int64_t)G * k + 1;   // ... iff r1 >= thr
-    if (rows < thr) return 0;
-    return nrb - (int)((thr + kMultiRows - 1) / kMultiRows - 1);
+    if (x - 1 <= sq.x) return nrb;             // E >= x iff (r1 - 1) / G >= k
+    const uint32_t k = (uint32_t)(x - 1) - (uint32_t)sq.x;
+    return k < (uint32_t)sq.y ? nrb - (int)((uint32_t)G * k / kMultiRows) : 0;   // ... iff r1 > G k
   };
-  auto count = [&](int x) {
-    int c = 0;
-    for (int b = lane; b < batch; b += 64)
-      if (in_set(b)) c += at_least(s_sq[b], s_key[b], x);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
-    return c;   // the same in every lane
+  // The sum over the set's sequences of f(b, {L - n, n}, key), in every lane: the first
+  // 64 from registers.  f(lanes past the batch) is not used.
+  auto in_set = [&](int b) { return b < batch && (by_class && batch > 64 ? b % ncls == my_cls : mine); };
+  auto each = [&](auto f) {
+    if (in_set(lane)) f(sq0, key0);
+    for (int b = lane + 64; b < batch; b += 64)
+      if (in_set(b)) f(s_sq[b], s_key[b]);
   };
-  const int set_items = count(0) * hx;
+  auto total = [&](int c) { return __builtin_amdgcn_readlane(wave_scan(c), 63); };
+  int set_items = 0;
+  each([&](int2 sq, int) { set_items += (sq.y * G + kMultiRows - 1) / kMultiRows; });
+  set_items = total(set_items) * hx;
 
   if (t_first >= set_items) return;
   const int v = t_first / hx, hsub = t_first - v * hx;
   int b = 0, rb = 0;
   {
-    int lo = 0, hi = cap + 1, chi = 0;   // C(lo) > v >= C(hi) = chi
+    int lo = 0, hi = emax + 1, chi = 0;   // C(lo) > v >= C(hi) = chi
     while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      const int c = count(mid);
-      if (c > v) {
-        lo = mid;
+      // Three points strictly between where there is room (else some coincide).
+      const int d = hi - lo, x2 = lo + (d >> 1), x1 = lo + max(d >> 2, 1), x3 = min(x2 + max(d >> 2, 1), hi - 1);
+      int c1 = 0, c2 = 0, c3 = 0;
+      each([&](int2 sq, int key) {
+        c1 += at_least(sq, key, x1);
+        c2 += at_least(sq, key, x2);
+        c3 += at_least(sq, key, x3);
+      });
+      c1 = total(c1);
+      c2 = total(c2);
+      c3 = total(c3);
+      if (c3 > v) {
+        lo = x3;
       } else {
-        hi = mid;
-        chi = c;
+        hi = x3;
+        chi = c3;
+        if (c2 > v) {
+          lo = x2;
+        } else {
+          hi = x2;
+          chi = c2;
+          if (c1 > v) {
+            lo = x1;
+          } else {
+            hi = x1;
+            chi = c1;
+          }
+        }
       }
     }
     // Among the items with exactly lo keys, the (v - chi)-th in sequence order.
@@ -292,20 +307,14 @@ void multi_query_kernel(const Params p) {
     for (int b0 = 0; b0 < batch && !found; b0 += 64) {
       const int bb = b0 + lane;
       int c1 = 0, c2 = 0, nrb = 0;
-      if (bb < batch && in_set(bb)) {
-        const int2 sq = s_sq[bb];
-        const int key = s_key[bb];
-        c1 = at_least(sq, key, lo);
+      if (in_set(bb)) {
+        const int2 sq = b0 ? s_sq[bb] : sq0;
+        const int key = b0 ? s_key[bb] : key0;
+        nrb = (sq.y * G + kMultiRows - 1) / kMultiRows;
+        c1 = lo > 0 ? at_least(sq, key, lo) : nrb;
         c2 = at_least(sq, key, lo + 1);
-        nrb = (sq.y + kMultiRows - 1) / kMultiRows;
       }
-      const int eq = c1 - c2;
-      int incl = eq;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-      }
+      const int eq = c1 - c2, incl = wave_scan(eq);
       const uint64_t hit = __builtin_amdgcn_ballot_w64(j >= incl - eq && j < incl);
       if (hit) {
         const int src = __builtin_ctzll(hit);
@@ -323,8 +332,9 @@ void multi_query_kernel(const Params p) {
   // head fixes the page tiles' offset, and with it their HBM channels).
   const int g = by_head ? ((xcd + b) & 7) + 8 * hsub : (by_class ? (xcd + b) % Hkv : hsub);
   const int q0 = p.q_start[b];
-  const int2 sqb = s_sq[b];
-  const int n = sqb.y / G;
+  const int2 sqb = batch > 64 ? make_int2(uni(s_sq[b].x), uni(s_sq[b].y))
+                              : make_int2(__builtin_amdgcn_readlane(sq0.x, b), __builtin_amdgcn_readlane(sq0.y, b));
+  const int n = sqb.y;
   const int L = sqb.x + n;
   const int rows = n * G;
   const int r0 = rb * kMultiRows, r1 = min(r0 + kMultiRows, rows);
