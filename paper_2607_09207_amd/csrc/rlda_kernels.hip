@@ -132,6 +132,26 @@ __device__ __forceinline__ float group_sum(float x) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// Max / sum over the 16 lanes with the same l & 3, every lane getting the result:
+// rotations by 8 and 4 within rows of 16, then the lane swaps.  (A page's reductions by
+// LDS shuffles were most of its time in the fp32 stream: the smallest call, 8 sequences
+// of up to 256 tokens, 7.2 us a call with them, 6.2 so.)
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+  const int v = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float token_max(float x) {
+  x = fmaxf(x, dpp_move<0x128>(x));   // row_ror:8, 4
+  x = fmaxf(x, dpp_move<0x124>(x));
+  return group_max(x);
+}
+__device__ __forceinline__ float token_sum(float x) {
+  x += dpp_move<0x128>(x);
+  x += dpp_move<0x124>(x);
+  return group_sum(x);
+}
+
 // ---------------------------------------------------------------- helpers
 
 // Index of block b < n such that each of the 8 XCDs (block b runs on XCD b % 8) gets a
@@ -702,13 +722,10 @@ struct Valu {
       float s = 0.f;
 #pragma unroll
       for (int j = 0; j < CW; ++j) s += qv[h][j] * __uint_as_float(f.k[j >> 2][j & 3]);
-      s += __shfl_xor(s, 1);
-      s += __shfl_xor(s, 2);
+      s += dpp_move<0xB1>(s);   // lane ^ 1
+      s += dpp_move<0x4E>(s);   // lane ^ 2
       s = valid ? s * kmul : neg_inf();
-      float mx = s;
-#pragma unroll
-      for (int o = 4; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-      const float mn = fmaxf(m[h], mx);
+      const float mn = fmaxf(m[h], token_max(s));
       const float mu = (mn == neg_inf()) ? 0.f : mn;
       const float alpha = __builtin_amdgcn_exp2f(m[h] - mu);
       const float pr = __builtin_amdgcn_exp2f(s - mu);
@@ -723,17 +740,9 @@ struct Valu {
   __device__ __forceinline__ void reduce_tokens(float* lt) {
 #pragma unroll
     for (int h = 0; h < GM; ++h) {
-      float a = l[h];
+      lt[h] = token_sum(l[h]);
 #pragma unroll
-      for (int o = 4; o < 64; o <<= 1) a += __shfl_xor(a, o);
-      lt[h] = a;
-#pragma unroll
-      for (int j = 0; j < CW; ++j) {
-        float v = acc[h][j];
-#pragma unroll
-        for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o);
-        acc[h][j] = v;
-      }
+      for (int j = 0; j < CW; ++j) acc[h][j] = token_sum(acc[h][j]);
     }
   }
 
