@@ -18,6 +18,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr float kRescaleLog2 = 8.f;          // lazy-rescale threshold of the online softmax (log2 units)
 constexpr uint32_t kRsrcWord3 = 0x00020000u; // raw buffer, 32-bit data format
 constexpr int kLoadNT = 2;                   // cache policy: non-temporal (KV is read once)
+constexpr int kVmcnt0 = 0x0F70;             // s_waitcnt: no vector memory operation outstanding
 constexpr int kPastRange = 0x40000000;       // buffer offset beyond any descriptor's records: reads 0
 
 __device__ __forceinline__ float neg_inf() { return -__builtin_huge_valf(); }

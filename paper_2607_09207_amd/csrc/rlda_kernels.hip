@@ -1375,6 +1375,17 @@ void decode_attention_kernel(const Params p) {
     // the chunk starting at position cbase, `nxt` the one after it (fetched a whole
     // chunk ahead).  The ring runs across chunk boundaries, so it drains only at
     // the end of the quarter.
+    //   kIdsWaited: ids are waited for where they are fetched, once a chunk.  Left in
+    // flight, the compiler has to take them for the newest loads wherever an id may be
+    // read, and waits for every page in flight before each issue: one page ahead is what
+    // then remains.  us a call, left in flight / waited for:
+    //   four sequences of 8k-16k tokens 31.4 / 30.3, long-tailed bf16 78.0 / 77.3, after
+    //   the prompt pass 119.8 / 118.7, verification 92.3 / 91.2 (fp8 82.4 / 80.3), packed
+    //   groups at d = 64 91.6 / 84.1 and 25.6 / 24.4;
+    //   two workgroups per CU (fp8 long-tailed 223.4 / 228.1, d = 64 43.8 / 44.3), the
+    //   fp32 stream (11.6 / 11.8) and packed groups at d = 128 (79.7 / 80.1) have enough
+    //   in flight with one page ahead, and more of them at once costs bandwidth.
+    constexpr bool kIdsWaited = WPE == 1 && Pol::kQRing && !(PACK && D == 128);
     const int cn = w1 - w0;   // positions of this quarter (relative index k)
     // The unit of a chunk's last position bounds the units of the next chunk from below.
     auto unit_of_info = [](int info) { return (info >> kInfoSeqShift) & (PACK ? 4095 : 8191); };
@@ -1383,7 +1394,11 @@ void decode_attention_kernel(const Params p) {
                                                   Hs, nrc, hint)
                        : StreamChunk{-1, 0};
     };
-    StreamChunk cur = fetch(w0, wunit), nxt = {-1, 0};   // nxt: fetched once the first loads are out
+    StreamChunk cur = fetch(w0, wunit), nxt = {-1, 0};
+    if constexpr (kIdsWaited) {
+      if (cn > kChunk) nxt = fetch(w0 + kChunk, unit_of_info(__builtin_amdgcn_readlane(cur.info, kChunk - 1)));
+      __builtin_amdgcn_s_waitcnt(kVmcnt0);
+    }
     int cbase = 0;   // relative position of cur's first entry
     {
       typename Pol::Frag fr[kDepth];
@@ -1520,13 +1535,15 @@ void decode_attention_kernel(const Params p) {
           cur = nxt;
           cbase += kChunk;
           nxt = fetch(w0 + cbase + kChunk, unit_of_info(__builtin_amdgcn_readlane(cur.info, kChunk - 1)));
+          if constexpr (kIdsWaited) __builtin_amdgcn_s_waitcnt(kVmcnt0);
         }
       };
 #pragma unroll
       for (int k = 0; k < kDepth - 1; ++k)
         if (k < cn) issue(fr[k], sinfo[k], skm[k], svm[k], qring[k], pring[k], k);
       // First read kChunk - kDepth + 1 positions from now.
-      nxt = fetch(w0 + kChunk, unit_of_info(__builtin_amdgcn_readlane(cur.info, kChunk - 1)));
+      if constexpr (!kIdsWaited)
+        nxt = fetch(w0 + kChunk, unit_of_info(__builtin_amdgcn_readlane(cur.info, kChunk - 1)));
       int i = 0;
       // Steady state: every position issued lies inside the quarter.
       for (; i + 2 * kDepth - 2 < cn; i += kDepth) {
