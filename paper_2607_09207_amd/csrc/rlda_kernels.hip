@@ -504,7 +504,8 @@ struct Mfma {
     compute_with<MULTI>(f, nullptr, lane, valid_tokens, kmul, vmul);
   }
   // ... with the page's V operands built once by the caller (vo), or here (null).
-  template <bool MULTI = false>
+  // EXACT: the probabilities enter the product as a bf16 value and a bf16 remainder.
+  template <bool MULTI = false, bool EXACT = false>
   __device__ __forceinline__ void compute_with(const Frag& f, const VOp* vo, int lane, int valid_tokens, float kmul,
                                                float vmul) {
     const int qg = lane >> 4;
@@ -549,8 +550,26 @@ struct Mfma {
     u32x2 pb2 = {pack_bf16(pr[0] * vmul, pr[1] * vmul), pack_bf16(pr[2] * vmul, pr[3] * vmul)};
     const s16x4 pb = __builtin_bit_cast(s16x4, pb2);
     const VOp v = vo ? *vo : v_operand(f);
+    if constexpr (EXACT) {
+      // One 16x16x32 product over {V, V} and {probabilities, remainders} a tile.
+      float lo[4];
 #pragma unroll
-    for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v.a[t], pb, acc[t], 0, 0, 0);
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t hi = (r & 1) ? pb2[r >> 1] & 0xFFFF0000u : pb2[r >> 1] << 16;
+        lo[r] = pr[r] * vmul - __uint_as_float(hi);
+        if constexpr (FP8) lo[r] = fminf(lo[r], 3e38f);   // an infinite factor: no NaN from inf - inf
+      }
+      const bf16x8 pq = __builtin_bit_cast(bf16x8, u32x4{pb2[0], pb2[1], pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])});
+#pragma unroll
+      for (int t = 0; t < DT; ++t) {
+        const u32x2 a = __builtin_bit_cast(u32x2, v.a[t]);
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{a[0], a[1], a[0], a[1]}), pq,
+                                                         acc[t], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v.a[t], pb, acc[t], 0, 0, 0);
+    }
   }
 
   // One page against N tiles of rows, t[0 .. N - 1] (every key visible to every row:
@@ -877,6 +896,12 @@ __device__ __forceinline__ StreamChunk fetch_chunk(const Params& p, const int32_
 // same loads for every page (past the last one with descriptors of no records), so a
 // wave waits for the page it consumes only and keeps kDepth pages in flight.  What
 // bounds it is latency: lengths, ids and the first page are three dependent round trips.
+//   A wave's stream is longer here than under equal shares, and only a stream's largest
+// probability is exact in bf16, so the product takes their remainders as well.  Error
+// against float64, fp32 outputs, 40/8 heads, d = 64, two sequences of 1.1k and 1.2k
+// tokens: equal shares 1.0e-3, whole segments 1.6e-3 without the remainders (11.4 us a
+// call) and 2.4e-6 with them (12.0 us; append + decode of 32 short fp8 sequences 16.7 and
+// 18.5).
 template <class Pol>
 __device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int nb, int tail,
                                               float (*sacc)[16][Pol::kD + 4], float (*sml)[16][2]) {
@@ -925,7 +950,12 @@ __device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int
       for (int k = 0; k < kDepth; ++k) {
         const int si = (k + kDepth - 1) % kDepth;
         issue(fr[si], sval[si], skm[si], svm[si], i + k + kDepth - 1);
-        if (i + k < cn) st.compute(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
+        if (i + k < cn) {
+          if constexpr (Pol::kQRing)
+            st.template compute_with<false, true>(fr[k], nullptr, lane, sval[k], p.scale_log2 * skm[k], svm[k]);
+          else
+            st.compute(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
+        }
       }
     }
   }

@@ -68,3 +68,16 @@ def test_default_shares_of_packed_groups(torch_cuda, prompt):
     got, flags = run_grouped(torch_cuda, w, 4, [prompt // 16] * 2)
     assert flags == 0
     assert_close(got, oracle.run(w), "bf16", f"packed prompt={prompt}")
+
+
+@pytest.mark.parametrize("name", ["few_pages_bf16", "few_pages_fp8", "few_pages_d64", "second_id_chunk_fp8"])
+def test_whole_segments_keep_the_probabilities_remainders(torch_cuda, name):
+    """A probability and its bf16 remainder carry 16 bits (relative error 2^-17 each), so an
+    output is off by at most 2^-17 max|v|; fp32 scores and sums of up to 4170 keys add less
+    than that again.  Without the remainders the error is about 2^-9 max|v| / sqrt(keys)."""
+    kv, Hq, Hkv, d, lens = CASES[name]
+    w = I.make_custom(lens, Hq, Hkv, d, kv_dtype=kv, seed=74, extra_pages=2)
+    got, flags = gpu_run(torch_cuda, w, tag=f"remainders {name}")
+    assert flags == 0
+    worst = float(np.max(np.abs(got - oracle.run(w))))
+    assert worst <= 2.0 ** -16 * 6.0, worst   # |v| < 6: normal values
