@@ -276,8 +276,9 @@ rlda_status rl_decode_attn_append(rl_decode_attn_t handle, int32_t batch, int32_
  *                n_b > max_q_len then gets no rows and raises flag bit 1.  Otherwise
  *                the (token, head) pairs of one (sequence, KV head) are processed 128
  *                at a time by one workgroup as 32x32 MFMA tiles (each K/V page read
- *                once per 128 rows), batch <= 4096, and only the flag word of the
- *                workspace is used.
+ *                once per 128 rows; 32 at a time, the keys split over the workgroup's
+ *                waves, on calls of few rows), batch <= 4096, and only the flag word of
+ *                the workspace is used.
  *   other arrays and `workspace` as for rl_decode_attn_run.
  * Supported for bf16 and fp8 caches (RLDA_ERR_UNSUPPORTED for f32, and when q
  * holds 2^31 bytes or more).  Device-side checks: a sequence with inconsistent
