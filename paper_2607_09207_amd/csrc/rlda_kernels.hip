@@ -557,7 +557,8 @@ struct Mfma {
       for (int r = 0; r < 4; ++r) {
         const uint32_t hi = (r & 1) ? pb2[r >> 1] & 0xFFFF0000u : pb2[r >> 1] << 16;
         lo[r] = pr[r] * vmul - __uint_as_float(hi);
-        if constexpr (FP8) lo[r] = fminf(lo[r], 3e38f);   // an infinite factor: no NaN from inf - inf
+        // A product whose bf16 value is infinite: a finite remainder, no NaN from inf - inf.
+        if constexpr (FP8) lo[r] = fmaxf(fminf(lo[r], 3e38f), -3e38f);
       }
       const bf16x8 pq = __builtin_bit_cast(bf16x8, u32x4{pb2[0], pb2[1], pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])});
 #pragma unroll
@@ -632,6 +633,17 @@ struct Mfma {
     for (int c = 0; c < DT; ++c)
 #pragma unroll
       for (int r = 0; r < N; ++r) t[r].acc[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v.a[c], pb[r], t[r].acc[c], 0, 0, 0);
+  }
+
+  // Whether remainders may have made a NaN: with an infinite V (bf16 caches; E4M3 has
+  // none) a remainder of 0 or of the other sign does.  Such a stream is run again without.
+  __device__ __forceinline__ bool remainders_failed() const {
+    bool nan = false;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) nan = nan || acc[t][r] != acc[t][r];
+    return !FP8 && __builtin_amdgcn_ballot_w64(nan) != 0;
   }
 
   // Write this wave's state in canonical [head][d] form to LDS.
@@ -915,48 +927,59 @@ __device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int
   typename Pol::QOp qo;
   Pol::load_q(qo, p, b, g, lane, true);
   st.begin(qo, p, b, g, lane);
-  for (int cb = j0; cb < j1; cb += kChunk) {
-    const int cn = min(kChunk, j1 - cb);
-    if (cb > j0) pid = bt[cb + min(lane, cn - 1)];
-    typename Pol::Frag fr[kDepth];
-    float skm[kDepth], svm[kDepth];
-    int sval[kDepth];
-    auto issue = [&](typename Pol::Frag& f, int& val, float& ks, float& vs, int k) {
-      int pk = -1;
-      if (k < cn) {
-        pk = __builtin_amdgcn_readlane(pid, k);
-        if ((unsigned)pk >= (unsigned)p.num_pages) {   // not a page of the pool: contributes nothing
-          if (lane == 0) atomicOr(p.flags, kFlagBadPage);
-          pk = -1;
+  auto stream = [&](auto exact) {   // exact: with the remainders
+    for (int cb = j0; cb < j1; cb += kChunk) {
+      const int cn = min(kChunk, j1 - cb);
+      if (cb > j0) pid = bt[cb + min(lane, cn - 1)];
+      typename Pol::Frag fr[kDepth];
+      float skm[kDepth], svm[kDepth];
+      int sval[kDepth];
+      auto issue = [&](typename Pol::Frag& f, int& val, float& ks, float& vs, int k) {
+        int pk = -1;
+        if (k < cn) {
+          pk = __builtin_amdgcn_readlane(pid, k);
+          if ((unsigned)pk >= (unsigned)p.num_pages) {   // not a page of the pool: contributes nothing
+            if (lane == 0) atomicOr(p.flags, kFlagBadPage);
+            pk = -1;
+          }
+        }
+        val = pk < 0 ? 0 : (cb + k == nb - 1 ? tail : kPage);
+        const int64_t po = (pk >= 0) ? (int64_t)pk * p.stride_page + (int64_t)g * p.stride_head : 0;
+        const uint32_t nrec = val > 0 ? (uint32_t)((val - 1) * p.stride_slot + D * Pol::kEB) : 0u;
+        ks = 1.f;
+        vs = 1.f;
+        if constexpr (Pol::kFp8) {
+          const int64_t si = (pk >= 0) ? (int64_t)pk * p.num_kv_heads + g : 0;
+          const uint32_t sb = (pk >= 0) ? 4u : 0u;
+          ks = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.k_scale + si, sb), 0, 0, 0));
+          vs = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.v_scale + si, sb), 0, 0, 0));
+        }
+        st.issue(f, make_rsrc_uni((const char*)p.k + po, nrec), make_rsrc_uni((const char*)p.v + po, nrec));
+      };
+#pragma unroll
+      for (int k = 0; k < kDepth - 1; ++k) issue(fr[k], sval[k], skm[k], svm[k], k);
+      for (int i = 0; i < cn; i += kDepth) {
+#pragma unroll
+        for (int k = 0; k < kDepth; ++k) {
+          const int si = (k + kDepth - 1) % kDepth;
+          issue(fr[si], sval[si], skm[si], svm[si], i + k + kDepth - 1);
+          if (i + k < cn) {
+            if constexpr (Pol::kQRing)
+              st.template compute_with<false, decltype(exact)::value>(fr[k], nullptr, lane, sval[k], p.scale_log2 * skm[k],
+                                                                      svm[k]);
+            else
+              st.compute(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
+          }
         }
       }
-      val = pk < 0 ? 0 : (cb + k == nb - 1 ? tail : kPage);
-      const int64_t po = (pk >= 0) ? (int64_t)pk * p.stride_page + (int64_t)g * p.stride_head : 0;
-      const uint32_t nrec = val > 0 ? (uint32_t)((val - 1) * p.stride_slot + D * Pol::kEB) : 0u;
-      ks = 1.f;
-      vs = 1.f;
-      if constexpr (Pol::kFp8) {
-        const int64_t si = (pk >= 0) ? (int64_t)pk * p.num_kv_heads + g : 0;
-        const uint32_t sb = (pk >= 0) ? 4u : 0u;
-        ks = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.k_scale + si, sb), 0, 0, 0));
-        vs = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.v_scale + si, sb), 0, 0, 0));
-      }
-      st.issue(f, make_rsrc_uni((const char*)p.k + po, nrec), make_rsrc_uni((const char*)p.v + po, nrec));
-    };
-#pragma unroll
-    for (int k = 0; k < kDepth - 1; ++k) issue(fr[k], sval[k], skm[k], svm[k], k);
-    for (int i = 0; i < cn; i += kDepth) {
-#pragma unroll
-      for (int k = 0; k < kDepth; ++k) {
-        const int si = (k + kDepth - 1) % kDepth;
-        issue(fr[si], sval[si], skm[si], svm[si], i + k + kDepth - 1);
-        if (i + k < cn) {
-          if constexpr (Pol::kQRing)
-            st.template compute_with<false, true>(fr[k], nullptr, lane, sval[k], p.scale_log2 * skm[k], svm[k]);
-          else
-            st.compute(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
-        }
-      }
+    }
+  };
+  stream(std::true_type{});
+  if constexpr (Pol::kQRing) {
+    if (st.remainders_failed()) {
+      pid = bt[j0 + min(lane, j1 - j0 - 1)];   // a stream without pages has no NaN
+      st.begin(st.q, p, b, g, lane);
+      stream(std::false_type{});
     }
   }
   st.to_lds(sacc[wave], sml[wave], lane);

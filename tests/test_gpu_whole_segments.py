@@ -9,6 +9,8 @@ as many segments as workgroups and one more, a long segment among short ones, on
 segment alone.  Every output is compared with the fp64 oracle; the multi-token and the
 packed grouped call take the same choice.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -81,3 +83,25 @@ def test_whole_segments_keep_the_probabilities_remainders(torch_cuda, name):
     assert flags == 0
     worst = float(np.max(np.abs(got - oracle.run(w))))
     assert worst <= 2.0 ** -16 * 6.0, worst   # |v| < 6: normal values
+
+
+@pytest.mark.parametrize("name", ["few_pages_bf16", "few_pages_d64"])
+def test_infinite_values_stay_infinite(torch_cuda, name):
+    """An infinite V times a probability is that infinity, whatever share of a call its
+    sequence gets (0 times it, or two of unlike sign, would be NaN): the outputs are
+    infinite, NaN and finite where the oracle's are."""
+    kv, Hq, Hkv, d, lens = CASES[name]
+    w = I.make_custom(lens, Hq, Hkv, d, kv_dtype=kv, seed=75, extra_pages=2)
+    v, PINF, NINF = w.v_cache.copy(), 0x7F80, 0xFF80
+    for b in np.flatnonzero(w.seq_lens > 16):
+        for token, col, bits in ((0, 5, PINF), (9, 6, NINF), (w.seq_lens[b] - 1, 7, PINF), (3, 9, PINF), (16, 9, NINF)):
+            v[w.block_table[b, token // 16], :, token % 16, col] = bits
+    w = dataclasses.replace(w, v_cache=v)
+    want = oracle.run(w)
+    finite = np.isfinite(want)
+    assert np.isposinf(want).any() and np.isneginf(want).any() and np.isnan(want).any()
+    for ranges in (0, 5):
+        got, flags = gpu_run(torch_cuda, w, ranges=ranges, tag=f"infinite {name}")
+        assert flags == 0
+        assert np.array_equal(got[~finite], want[~finite], equal_nan=True), f"ranges={ranges}"
+        assert np.max(np.abs(got[finite] - want[finite])) <= TOL[kv]
