@@ -277,6 +277,7 @@ __device__ __forceinline__ void merge_pieces(const Params& p, int orow, int qh, 
 // V fragment: lane l holds rows 4q..4q+3, elements [D/16*i, D/16*(i+1)).
 // Score tile (D layout of 16x16 MFMA): lane l holds S[token 4q+r][head i].
 // Output tile dt: lane l holds O[head i][d = D/16*(4q+r) + dt].
+enum Remainders { kAlways, kByCall };
 template <int D, bool FP8>
 struct Mfma {
   static constexpr int kD = D;
@@ -499,15 +500,17 @@ struct Mfma {
 
   // Page with index `j` in its sequence; `valid_tokens` tokens of it count (for
   // multi-token rows: tokens of the page and after it, up to 31, less `shift`).
-  template <bool MULTI = false>
-  __device__ __forceinline__ void compute(const Frag& f, int lane, int valid_tokens, float kmul, float vmul) {
-    compute_with<MULTI>(f, nullptr, lane, valid_tokens, kmul, vmul);
+  //   Remainders: the probabilities enter the product as a bf16 value and a bf16
+  // remainder.  kAlways: in one product; kByCall: where `exact` (0 or ~0, uniform) says so.
+  template <bool MULTI = false, Remainders REM = kByCall>
+  __device__ __forceinline__ void compute(const Frag& f, int lane, int valid_tokens, float kmul, float vmul,
+                                          uint64_t exact = 0) {
+    compute_with<MULTI, REM>(f, nullptr, lane, valid_tokens, kmul, vmul, exact);
   }
   // ... with the page's V operands built once by the caller (vo), or here (null).
-  // EXACT: the probabilities enter the product as a bf16 value and a bf16 remainder.
-  template <bool MULTI = false, bool EXACT = false>
+  template <bool MULTI = false, Remainders REM = kByCall>
   __device__ __forceinline__ void compute_with(const Frag& f, const VOp* vo, int lane, int valid_tokens, float kmul,
-                                               float vmul) {
+                                               float vmul, uint64_t exact) {
     const int qg = lane >> 4;
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -526,8 +529,9 @@ struct Mfma {
     // same relative rounding in bf16), and the accumulator rescale, which reads
     // and writes every accumulator register, is skipped on almost every page.
     const bool up = mx > m + kRescaleLog2;   // always when m is still -inf and mx is not
-    if (__builtin_amdgcn_ballot_w64(up) != 0)
-    {
+    const uint64_t rescale = __builtin_amdgcn_ballot_w64(up);
+    // One branch for the two rare cases, so that neither costs the ordinary page another.
+    if ((REM == kByCall ? rescale | exact : rescale) != 0) {
       // Multi-token rows: a row whose keys are all masked so far keeps m = -inf
       // while other rows move, so alpha comes from `up` (1 otherwise).
       const float mn = up ? mx : m;
@@ -535,8 +539,13 @@ struct Mfma {
                                 : __builtin_amdgcn_exp2f(m - mn);   // 0 from -inf, 1 when unchanged
       l *= alpha;
       m = mn;
+      if (rescale != 0) {
 #pragma unroll
-      for (int t = 0; t < DT; ++t) acc[t] *= alpha;
+        for (int t = 0; t < DT; ++t) acc[t] *= alpha;
+      }
+      if constexpr (REM == kByCall) {
+        if (exact != 0) add_remainders(vo ? *vo : v_operand(f), sv, vmul);
+      }
     }
     const float mu = (m == neg_inf()) ? 0.f : m;
     float pr[4];
@@ -547,30 +556,57 @@ struct Mfma {
       ps += pr[r];
     }
     l += ps;
-    u32x2 pb2 = {pack_bf16(pr[0] * vmul, pr[1] * vmul), pack_bf16(pr[2] * vmul, pr[3] * vmul)};
-    const s16x4 pb = __builtin_bit_cast(s16x4, pb2);
+    const u32x2 pb = {pack_bf16(pr[0] * vmul, pr[1] * vmul), pack_bf16(pr[2] * vmul, pr[3] * vmul)};
     const VOp v = vo ? *vo : v_operand(f);
-    if constexpr (EXACT) {
-      // One 16x16x32 product over {V, V} and {probabilities, remainders} a tile.
-      float lo[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t hi = (r & 1) ? pb2[r >> 1] & 0xFFFF0000u : pb2[r >> 1] << 16;
-        lo[r] = pr[r] * vmul - __uint_as_float(hi);
-        // A product whose bf16 value is infinite: a finite remainder, no NaN from inf - inf.
-        if constexpr (FP8) lo[r] = fmaxf(fminf(lo[r], 3e38f), -3e38f);
-      }
-      const bf16x8 pq = __builtin_bit_cast(bf16x8, u32x4{pb2[0], pb2[1], pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])});
+    if constexpr (REM == kAlways) {
+      // One 16x16x32 product over {V, finite V} and {probabilities, remainders} a tile.
+      const u32x2 lo = remainders(pr, vmul);
+      const bf16x8 pq = __builtin_bit_cast(bf16x8, u32x4{pb[0], pb[1], lo[0], lo[1]});
 #pragma unroll
       for (int t = 0; t < DT; ++t) {
-        const u32x2 a = __builtin_bit_cast(u32x2, v.a[t]);
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{a[0], a[1], a[0], a[1]}), pq,
+        const u32x2 a = __builtin_bit_cast(u32x2, v.a[t]), b = __builtin_bit_cast(u32x2, finite(v.a[t]));
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{a[0], a[1], b[0], b[1]}), pq,
                                                          acc[t], 0, 0, 0);
       }
     } else {
 #pragma unroll
-      for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v.a[t], pb, acc[t], 0, 0, 0);
+      for (int t = 0; t < DT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v.a[t], __builtin_bit_cast(s16x4, pb), acc[t], 0, 0, 0);
     }
+  }
+
+  // What the bf16 values of four probabilities (times the V scale) leave of them.
+  __device__ __forceinline__ static u32x2 remainders(const float* pr, float vmul) {
+    float lo[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      lo[r] = pr[r] * vmul - (float)(__bf16)(pr[r] * vmul);
+      // A product whose bf16 value is infinite: a finite remainder, no NaN from inf - inf.
+      if constexpr (FP8) lo[r] = fmaxf(fminf(lo[r], 3e38f), -3e38f);
+    }
+    return u32x2{pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])};
+  }
+
+  // V for the product with the remainders.  With an infinite V (bf16 caches; E4M3 has
+  // none) a remainder of 0 or of the other sign would make NaN of the output's infinity:
+  // |V| ends at 2^100 here, so that no sum of these overflows either.  (As integers, bf16
+  // values order like their magnitudes: the positive ones as signed integers, above
+  // every negative one, the negative ones as unsigned.)
+  __device__ __forceinline__ static s16x4 finite(s16x4 v) {
+    if constexpr (FP8) return v;
+    v = __builtin_elementwise_min(v, (s16x4)(short)0x7180);
+    return __builtin_bit_cast(s16x4, __builtin_elementwise_min(__builtin_bit_cast(u16x4, v), (u16x4)(unsigned short)0xF180));
+  }
+
+  // Add a page's remainders times V, for scores sv and the reference maximum m.
+  __device__ __forceinline__ void add_remainders(const VOp& v, const float* sv, float vmul) {
+    const float mu = (m == neg_inf()) ? 0.f : m;
+    float pr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pr[r] = __builtin_amdgcn_exp2f(sv[r] - mu);
+    const s16x4 lo = __builtin_bit_cast(s16x4, remainders(pr, vmul));
+#pragma unroll
+    for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(finite(v.a[t]), lo, acc[t], 0, 0, 0);
   }
 
   // One page against N tiles of rows, t[0 .. N - 1] (every key visible to every row:
@@ -633,17 +669,6 @@ struct Mfma {
     for (int c = 0; c < DT; ++c)
 #pragma unroll
       for (int r = 0; r < N; ++r) t[r].acc[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(v.a[c], pb[r], t[r].acc[c], 0, 0, 0);
-  }
-
-  // Whether remainders may have made a NaN: with an infinite V (bf16 caches; E4M3 has
-  // none) a remainder of 0 or of the other sign does.  Such a stream is run again without.
-  __device__ __forceinline__ bool remainders_failed() const {
-    bool nan = false;
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) nan = nan || acc[t][r] != acc[t][r];
-    return !FP8 && __builtin_amdgcn_ballot_w64(nan) != 0;
   }
 
   // Write this wave's state in canonical [head][d] form to LDS.
@@ -745,7 +770,8 @@ struct Valu {
     for (int s = 0; s < NL; ++s) f.v[s] = RowLoad<16>::load(rv, off + 16 * s);
   }
 
-  __device__ __forceinline__ void compute(const Frag& f, int lane, int valid_tokens, float kmul, float) {
+  template <bool MULTI = false, Remainders REM = kByCall>
+  __device__ __forceinline__ void compute(const Frag& f, int lane, int valid_tokens, float kmul, float, uint64_t = 0) {
     const int t = lane >> 2;
     const bool valid = t < valid_tokens;
 #pragma unroll
@@ -927,59 +953,44 @@ __device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int
   typename Pol::QOp qo;
   Pol::load_q(qo, p, b, g, lane, true);
   st.begin(qo, p, b, g, lane);
-  auto stream = [&](auto exact) {   // exact: with the remainders
-    for (int cb = j0; cb < j1; cb += kChunk) {
-      const int cn = min(kChunk, j1 - cb);
-      if (cb > j0) pid = bt[cb + min(lane, cn - 1)];
-      typename Pol::Frag fr[kDepth];
-      float skm[kDepth], svm[kDepth];
-      int sval[kDepth];
-      auto issue = [&](typename Pol::Frag& f, int& val, float& ks, float& vs, int k) {
-        int pk = -1;
-        if (k < cn) {
-          pk = __builtin_amdgcn_readlane(pid, k);
-          if ((unsigned)pk >= (unsigned)p.num_pages) {   // not a page of the pool: contributes nothing
-            if (lane == 0) atomicOr(p.flags, kFlagBadPage);
-            pk = -1;
-          }
-        }
-        val = pk < 0 ? 0 : (cb + k == nb - 1 ? tail : kPage);
-        const int64_t po = (pk >= 0) ? (int64_t)pk * p.stride_page + (int64_t)g * p.stride_head : 0;
-        const uint32_t nrec = val > 0 ? (uint32_t)((val - 1) * p.stride_slot + D * Pol::kEB) : 0u;
-        ks = 1.f;
-        vs = 1.f;
-        if constexpr (Pol::kFp8) {
-          const int64_t si = (pk >= 0) ? (int64_t)pk * p.num_kv_heads + g : 0;
-          const uint32_t sb = (pk >= 0) ? 4u : 0u;
-          ks = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.k_scale + si, sb), 0, 0, 0));
-          vs = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.v_scale + si, sb), 0, 0, 0));
-        }
-        st.issue(f, make_rsrc_uni((const char*)p.k + po, nrec), make_rsrc_uni((const char*)p.v + po, nrec));
-      };
-#pragma unroll
-      for (int k = 0; k < kDepth - 1; ++k) issue(fr[k], sval[k], skm[k], svm[k], k);
-      for (int i = 0; i < cn; i += kDepth) {
-#pragma unroll
-        for (int k = 0; k < kDepth; ++k) {
-          const int si = (k + kDepth - 1) % kDepth;
-          issue(fr[si], sval[si], skm[si], svm[si], i + k + kDepth - 1);
-          if (i + k < cn) {
-            if constexpr (Pol::kQRing)
-              st.template compute_with<false, decltype(exact)::value>(fr[k], nullptr, lane, sval[k], p.scale_log2 * skm[k],
-                                                                      svm[k]);
-            else
-              st.compute(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
-          }
+  for (int cb = j0; cb < j1; cb += kChunk) {
+    const int cn = min(kChunk, j1 - cb);
+    if (cb > j0) pid = bt[cb + min(lane, cn - 1)];
+    typename Pol::Frag fr[kDepth];
+    float skm[kDepth], svm[kDepth];
+    int sval[kDepth];
+    auto issue = [&](typename Pol::Frag& f, int& val, float& ks, float& vs, int k) {
+      int pk = -1;
+      if (k < cn) {
+        pk = __builtin_amdgcn_readlane(pid, k);
+        if ((unsigned)pk >= (unsigned)p.num_pages) {   // not a page of the pool: contributes nothing
+          if (lane == 0) atomicOr(p.flags, kFlagBadPage);
+          pk = -1;
         }
       }
-    }
-  };
-  stream(std::true_type{});
-  if constexpr (Pol::kQRing) {
-    if (st.remainders_failed()) {
-      pid = bt[j0 + min(lane, j1 - j0 - 1)];   // a stream without pages has no NaN
-      st.begin(st.q, p, b, g, lane);
-      stream(std::false_type{});
+      val = pk < 0 ? 0 : (cb + k == nb - 1 ? tail : kPage);
+      const int64_t po = (pk >= 0) ? (int64_t)pk * p.stride_page + (int64_t)g * p.stride_head : 0;
+      const uint32_t nrec = val > 0 ? (uint32_t)((val - 1) * p.stride_slot + D * Pol::kEB) : 0u;
+      ks = 1.f;
+      vs = 1.f;
+      if constexpr (Pol::kFp8) {
+        const int64_t si = (pk >= 0) ? (int64_t)pk * p.num_kv_heads + g : 0;
+        const uint32_t sb = (pk >= 0) ? 4u : 0u;
+        ks = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.k_scale + si, sb), 0, 0, 0));
+        vs = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(make_rsrc_uni(p.v_scale + si, sb), 0, 0, 0));
+      }
+      st.issue(f, make_rsrc_uni((const char*)p.k + po, nrec), make_rsrc_uni((const char*)p.v + po, nrec));
+    };
+#pragma unroll
+    for (int k = 0; k < kDepth - 1; ++k) issue(fr[k], sval[k], skm[k], svm[k], k);
+    for (int i = 0; i < cn; i += kDepth) {
+#pragma unroll
+      for (int k = 0; k < kDepth; ++k) {
+        const int si = (k + kDepth - 1) % kDepth;
+        issue(fr[si], sval[si], skm[si], svm[si], i + k + kDepth - 1);
+        if (i + k < cn)
+          st.template compute<false, kAlways>(fr[k], lane, sval[k], p.scale_log2 * skm[k], svm[k]);
+      }
     }
   }
   st.to_lds(sacc[wave], sml[wave], lane);
@@ -1365,6 +1376,14 @@ void decode_attention_kernel(const Params p) {
   // 3. This workgroup's share [r0, r1) of the flattened (sequence, KV head, page)
   //    list, and this wave's quarter [w0, w1) of it.  Each wave walks its own pieces
   //    without waiting for the others; a piece inside its quarter is written directly.
+  //    Longer streams than W equal shares would give round more probabilities, so their
+  //    remainders enter the product here too (see whole_segment).  Relative error against
+  //    float64 and us a call, bf16 d = 128, W equal shares / this cut without remainders /
+  //    with them: 4 rows of 4 sequences of up to 640 tokens (8/1 heads) 1.0e-3 36.0 /
+  //    1.6e-3 17.7 / 2.3e-6 20.9; one sequence of 3000 (8/1) 1.1e-3 46.9 / 1.6e-3 16.2 /
+  //    2.3e-6 17.0; packed groups of 4, prompt 128 (12/2) 1.0e-3 18.4 / 1.5e-3 12.2 /
+  //    2.2e-6 13.7.
+  const uint64_t exact = direct || W2 < W ? ~0ull : 0ull;
   int w0, w1, wunit = 0;   // wunit: the unit of position w0 (when w0 < T)
   int64_t r0, r1;
   if (direct) {
@@ -1423,7 +1442,6 @@ void decode_attention_kernel(const Params p) {
     QN qring[kDepth];
     typedef typename PromptState<Pol, PROMPT>::type PInit;
     PInit pring[kDepth];
-    bool began = false;   // the segment being accumulated began inside this quarter
     // Page ids and position info come kChunk positions per vector load: `cur` holds
     // the chunk starting at position cbase, `nxt` the one after it (fetched a whole
     // chunk ahead).  The ring runs across chunk boundaries, so it drains only at
@@ -1447,6 +1465,7 @@ void decode_attention_kernel(const Params p) {
                                                   Hs, nrc, hint)
                        : StreamChunk{-1, 0};
     };
+    bool began = false;   // the segment being accumulated began inside this quarter
     StreamChunk cur = fetch(w0, wunit), nxt = {-1, 0};
     if constexpr (kIdsWaited) {
       if (cn > kChunk) nxt = fetch(w0 + kChunk, unit_of_info(__builtin_amdgcn_readlane(cur.info, kChunk - 1)));
@@ -1543,26 +1562,26 @@ void decode_attention_kernel(const Params p) {
           const int act = (info >> kInfoActShift) & 7, tok = info & kInfoTok;
           // A tile none of whose rows the page serves is skipped (its state would not change).
           if constexpr (NT == 1) {
-            st.template compute<true>(f, lane, (act == kActAll || rmem == act) ? tok : 0, p.scale_log2 * km, vm);
+            st.template compute<true>(f, lane, (act == kActAll || rmem == act) ? tok : 0, p.scale_log2 * km, vm, exact);
           } else {
             const typename Pol::VOp vo = Pol::v_operand(f);
             if (act == kActAll || act * G < 16)
               st.template compute_with<true>(f, &vo, lane, (act == kActAll || rmem == act) ? tok : 0,
-                                             p.scale_log2 * km, vm);
+                                             p.scale_log2 * km, vm, exact);
             if (act == kActAll || (act + 1) * G > 16)
               st2.template compute_with<true>(f, &vo, lane, (act == kActAll || rmem2 == act) ? tok : 0,
-                                              p.scale_log2 * km, vm);
+                                              p.scale_log2 * km, vm, exact);
           }
         } else if constexpr (MULTI) {
           if constexpr (NT == 1) {
-            st.template compute<true>(f, lane, info & kInfoTok, p.scale_log2 * km, vm);
+            st.template compute<true>(f, lane, info & kInfoTok, p.scale_log2 * km, vm, exact);
           } else {
             const typename Pol::VOp vo = Pol::v_operand(f);
-            st.template compute_with<true>(f, &vo, lane, info & kInfoTok, p.scale_log2 * km, vm);
-            st2.template compute_with<true>(f, &vo, lane, info & kInfoTok, p.scale_log2 * km, vm);
+            st.template compute_with<true>(f, &vo, lane, info & kInfoTok, p.scale_log2 * km, vm, exact);
+            st2.template compute_with<true>(f, &vo, lane, info & kInfoTok, p.scale_log2 * km, vm, exact);
           }
         } else
-          st.compute(f, lane, info & kInfoTok, p.scale_log2 * km, vm);
+          st.compute(f, lane, info & kInfoTok, p.scale_log2 * km, vm, exact);
         if (info & (kInfoLast | kInfoEnd)) {
           const bool ended = (info & kInfoLast) != 0;
           if (began && ended) {

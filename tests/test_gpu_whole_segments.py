@@ -85,6 +85,63 @@ def test_whole_segments_keep_the_probabilities_remainders(torch_cuda, name):
     assert worst <= 2.0 ** -16 * 6.0, worst   # |v| < 6: normal values
 
 
+# The other calls that get longer streams than one equal share a workgroup: rows of several
+# query tokens, packed groups, the attention launch after a (zero) prompt pass, and few
+# segments in fewer shares.
+LONGER = {
+    # (Hq, Hkv, lengths, query rows, group size, prompt tokens)
+    "rows_one_tile": (8, 2, [640, 200, 333, 17], 4, 0, 0),
+    "rows_two_tiles": (8, 1, [640, 200, 333, 17], 4, 0, 0),
+    "packed": (12, 2, [144, 200, 133, 129, 300, 128, 177, 190], 0, 4, 128),
+    "after_prompt_pass": (16, 1, [300, 17, 555, 100], 0, 4, 0),
+    "fewer_shares_one_segment": (8, 1, [3001], 0, 0, 0),
+    "fewer_shares_ragged": (12, 2, [9000, 5, 17, 300], 0, 0, 0),
+}
+
+
+def longer_call(torch, name, kv, d, change=None):
+    """The call's output, its flags and the oracle's output; `change` alters the inputs."""
+    Hq, Hkv, lens, rows, group, prompt = LONGER[name]
+    if rows:
+        w = I.make_multi(lens, [min(L, rows) for L in lens], Hq, Hkv, d, kv_dtype=kv, seed=76)
+    else:
+        w = I.make_custom(lens, Hq, Hkv, d, kv_dtype=kv, seed=76, shared_prefix=(group, prompt) if prompt else None)
+    w = change(w) if change else w
+    if rows:
+        return run_multi(torch, w, max_q_len=rows) + (oracle.run_multi(w),)
+    if group:
+        return run_grouped(torch, w, group, [prompt // 16] * (w.batch // group)) + (oracle.run(w),)
+    return gpu_run(torch, w, tag=name) + (oracle.run(w),)
+
+
+@pytest.mark.parametrize("kv,d", [("bf16", 128), ("bf16", 64), ("fp8_e4m3fn", 128), ("fp8_e4m3fn", 64)])
+@pytest.mark.parametrize("name", list(LONGER))
+def test_longer_streams_keep_the_remainders_too(torch_cuda, name, kv, d):
+    got, flags, want = longer_call(torch_cuda, name, kv, d)
+    assert flags == 0
+    worst = float(np.max(np.abs(got - want)))
+    assert worst <= 2.0 ** -16 * 6.0, worst   # as above
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("name", list(LONGER))
+def test_infinite_values_in_longer_streams(torch_cuda, name, d):
+    """Infinities among the first keys, which every row of the call sees."""
+    def change(w):
+        v = w.v_cache.copy()
+        for b in np.flatnonzero(w.seq_lens > 16):
+            for token, col, bits in ((0, 5, 0x7F80), (9, 6, 0xFF80), (3, 9, 0x7F80), (8, 9, 0xFF80)):
+                v[w.block_table[b, 0], :, token, col] = bits
+        return dataclasses.replace(w, v_cache=v)
+
+    got, flags, want = longer_call(torch_cuda, name, "bf16", d, change)
+    assert flags == 0
+    finite = np.isfinite(want)
+    assert np.isposinf(want).any() and np.isneginf(want).any() and np.isnan(want).any()
+    assert np.array_equal(got[~finite], want[~finite], equal_nan=True)
+    assert np.max(np.abs(got[finite] - want[finite])) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("name", ["few_pages_bf16", "few_pages_d64"])
 def test_infinite_values_stay_infinite(torch_cuda, name):
     """An infinite V times a probability is that infinity, whatever share of a call its
