@@ -69,7 +69,8 @@ def cpu_baseline(w, budget_s):
     return res
 
 
-KERNEL_SOURCES = ["paper_2607_09207_amd/csrc/rlda_kernels.hip", "paper_2607_09207_amd/csrc/rlda_device.h",
+KERNEL_SOURCES = ["paper_2607_09207_amd/csrc/rlda_kernels.hip", "paper_2607_09207_amd/csrc/rlda_split.h",
+                  "paper_2607_09207_amd/csrc/rlda_device.h",
                   "paper_2607_09207_amd/csrc/rlda_host.cpp",
                   "paper_2607_09207_amd/csrc/rlda_params.h"]
 

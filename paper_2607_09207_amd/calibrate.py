@@ -45,7 +45,7 @@ KV_CONFIGS = [
     ("mix_bf16_64x8_d128", 64, 8, 128, "bf16", "bf16"),
 ]
 # Sources whose hash stamps a fit (the decode kernel and its host side).
-KERNEL_SOURCES = ["csrc/rlda_kernels.hip", "csrc/rlda_device.h", "csrc/rlda_host.cpp", "csrc/rlda_params.h"]
+KERNEL_SOURCES = ["csrc/rlda_kernels.hip", "csrc/rlda_split.h", "csrc/rlda_device.h", "csrc/rlda_host.cpp", "csrc/rlda_params.h"]
 START_COST = 2   # the work split's price of a segment start, in pages (the library's default)
 BATCHES = (8, 32, 128, 512)
 LAWS = (("lognormal", 256, 1.0), ("lognormal", 1024, 1.0), ("lognormal", 4096, 0.7),

@@ -11,7 +11,7 @@
 //      sequences are therefore cut across many workgroups and short ones packed
 //      together: every workgroup streams the same work however long the tail of
 //      the length distribution is (Sec. 2.3 on long-tail decode).  Small calls take
-//      whole segments instead, one per workgroup (see "How the list is cut").
+//      whole segments instead, one per workgroup (see rlda_split.h).
 //   2. Page gather.  Each of the 4 waves of a workgroup takes a quarter of the
 //      share and walks it as one continuous stream of pages: its lanes decode 64
 //      positions at a time (sequence, KV head, page id, valid tokens, segment
@@ -56,6 +56,7 @@
 
 #include "rlda_device.h"
 #include "rlda_params.h"
+#include "rlda_split.h"
 
 // Flags, segment counters and partial slots of rl_decode_attn_run_noalloc, for
 // callers that cannot allocate device memory (layout in rlda_params.h).  Each GPU
@@ -153,13 +154,6 @@ __device__ __forceinline__ float token_sum(float x) {
 }
 
 // ---------------------------------------------------------------- helpers
-
-// Index of block b < n such that each of the 8 XCDs (block b runs on XCD b % 8) gets a
-// contiguous run of the indices.  A bijection of [0, n).
-__device__ __forceinline__ int xcd_contiguous(int b, int n) {
-  const int x = b & 7;
-  return x * (n >> 3) + min(x, n & 7) + (b >> 3);
-}
 
 __device__ __forceinline__ int64_t owner_of(int64_t x, int W, int64_t C) {
   // Largest u with floor(u*C/W) <= x: the share holding cost x.
@@ -1092,11 +1086,6 @@ void decode_attention_kernel(const Params p) {
   static_assert(kMaxQHeads <= kThreads, "one query head per thread");
   const int16_t qh0 = tid < p.num_q_heads ? p.q_head[tid] : (int16_t)0;
   const int W = p.nranges;
-  // Share index.  Workgroups are dispatched round-robin over the 8 XCDs (block b
-  // runs on XCD b % 8); each XCD gets a contiguous run of shares, so neighbouring
-  // work (the sequences of a GRPO group reading the same prompt pages, the pieces
-  // of one split segment) shares one L2.  A bijection of [0, W).
-  const int u = xcd_contiguous(blockIdx.x, W);
   const int batch = p.batch, Hkv = p.num_kv_heads, G = p.group;
   const int cap = p.max_pages * kPage;
   // Multi-token runs: nrc segments of 16 NT rows per (sequence, KV head), Hs per
@@ -1145,8 +1134,8 @@ void decode_attention_kernel(const Params p) {
       if ((b & (gs - 1)) == 0) s_gpp[b / gs] = (int16_t)pp;
     }
     if (head) s_ppre[b / P] = (b << 5) | P;
-    if (__builtin_amdgcn_ballot_w64(badl) != 0 && lane == 0 && u == 0) atomicOr(p.flags, kFlagBadLen);
-    if (__builtin_amdgcn_ballot_w64(live && (b & (gs - 1)) == 0 && want != pp) != 0 && lane == 0 && u == 0)
+    if (__builtin_amdgcn_ballot_w64(badl) != 0 && lane == 0 && blockIdx.x == 0) atomicOr(p.flags, kFlagBadLen);
+    if (__builtin_amdgcn_ballot_w64(live && (b & (gs - 1)) == 0 && want != pp) != 0 && lane == 0 && blockIdx.x == 0)
       atomicOr(p.flags, kFlagPrefixClamped);
     // Prefix sums of the packs' pages and of the non-empty packs, in pack order
     // (= lane order of the packs' first members).
@@ -1190,7 +1179,7 @@ void decode_attention_kernel(const Params p) {
         s_nfull[b] = (uint16_t)nf;
         s_tail[b] = (uint8_t)(L - (nf - 1) * kPage);
       }
-      if (bad && u == 0) atomicOr(p.flags, kFlagBadLen);
+      if (bad && blockIdx.x == 0) atomicOr(p.flags, kFlagBadLen);
       __syncthreads();
       for (int i = tid; i < ngroups; i += kThreads) {
         int mn = 0x7fffffff;
@@ -1199,7 +1188,7 @@ void decode_attention_kernel(const Params p) {
           mn = min(mn, (nf > 0 && s_tail[b] < kPage) ? nf - 1 : nf);   // full pages
         }
         const int want = i == tid ? want0 : p.prefix_pages[i], pp = max(0, min(want, mn));
-        if (want != pp && u == 0) atomicOr(p.flags, kFlagPrefixClamped);
+        if (want != pp && blockIdx.x == 0) atomicOr(p.flags, kFlagPrefixClamped);
         s_gpp[i] = (int16_t)pp;
       }
       __syncthreads();
@@ -1256,7 +1245,7 @@ void decode_attention_kernel(const Params p) {
         cnt += n > 0;
         most = max(most, n);
       }
-      if (bad && u == 0) atomicOr(p.flags, kFlagBadLen);
+      if (bad && blockIdx.x == 0) atomicOr(p.flags, kFlagBadLen);
       const int x = wave_scan(sum), xn = wave_scan(cnt), xm = wave_scan_max(most);
       if (lane == 63) {
         s_scan[wave] = x;
@@ -1297,7 +1286,7 @@ void decode_attention_kernel(const Params p) {
 
   // 2. Sequences with no pages left to stream: zero rows, or (grouped runs) the
   //    normalised prompt-pass result when the prompt is the whole sequence.
-  for (int b = u; b < nunits; b += W) {
+  for (int b = blockIdx.x; b < nunits; b += W) {
     if (s_pre[b + 1] != s_pre[b]) continue;
     if constexpr (MULTI) {
       // Rows of a sequence with no keys (none, or rows claimed past an empty cache).
@@ -1328,50 +1317,22 @@ void decode_attention_kernel(const Params p) {
     }
   }
 
-  // How the list is cut.  Uniform over the grid; calibrate.work_split mirrors it.  A run
-  // with a forced share count (inv_ranges 0) always takes W equal shares.
-  //   Whole segments: each workgroup takes one segment.  That skips the share search and
-  // the hand-off of cut pieces (store, count, read back), about 5 us together, and its
-  // waves stream (nbmax - fair) / 4 pages more than under equal shares of `fair` pages,
-  // 0.4 to 0.6 us each while so few of them run.  us a call on batches of equal lengths,
-  // equal shares against whole segments, 16 / 32 / 64 / 112 pages:
-  //   28/4 bf16 d 128, B = 4:   13.2 / 13.9 / 14.6 / 15.4   against  8.1 / 9.7 / 15.8 / 26.7
-  //                    B = 16:  11.2 / 12.4 / 14.3 / 17.5            8.2 / 10.3 / 17.7 / 28.7
-  //                    B = 32:  12.3 / 14.3 / 18.7 / 25.9            8.4 / 11.7 / 19.7 / 31.5
-  //   40/8 fp8 d 128,  B = 4:   14.2 / 14.5 / 14.9 / 15.5            7.4 / 9.5 / 14.3 / 21.5
-  //                    B = 32:  12.9 / 15.1 / 20.0 / 27.5            7.7 / 10.0 / 15.0 / 22.4
-  //   64/8 bf16 d 64,  B = 16:  10.9 / 12.3 / 14.4 / 17.7            6.5 / 8.2 / 12.2 / 18.3
-  // (28/4, B = 60, 200 pages: 68.6 against 62.3).  `over` is where the two meet, in pages
-  // over an equal share, by segments per workgroup: with one workgroup per CU whole
-  // segments leave CUs idle that could read, with two (half-size pages) they don't until
-  // half the workgroups are gone.  Multi-token, packed and prompt-state runs stream whole
-  // segments through the general loop, which is slower a page.
-  //   Equal shares hold at least 4 pages (one a wave), and so many that the largest
-  // segment falls into about 16 pieces, one batch of its final merge; of longer segments
-  // at least sqrt(1.25 nbmax), where pages and pieces cost alike (a share's page 0.15 us,
-  // a piece 0.19 us).  12/2 heads, one sequence of 112 pages: 31.3 us in 256 shares, 13.5
-  // so.  Where that bound holds the shares are a multiple of the segments, so that equal
-  // segments are cut alike.
+  // How the list is cut (rlda_split.h); uniform over the grid.
   const int nseg = nunits * Hs;
-  int W2 = W;   // equal shares used
-  bool direct = false;
-  if (p.inv_ranges > 0.f) {
-    int nbm = 0;
+  int nbm = 0;   // pages of the largest segment
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) nbm = max(nbm, s_scan_max[w]);
-    const float nb = (float)nbm, fair = (float)(int)C * p.inv_ranges, segs = (float)nseg * p.inv_ranges;
-    const float over = (MULTI || PROMPT)  ? fmaxf(40.f - 48.f * segs, 20.f)
-                       : !Pol::kHalfPages ? fmaxf(54.f - 72.f * segs, 26.f)
-                                          : (D == 64 ? 78.f : 57.f) + fmaxf(80.f * segs - 20.f, 0.f);
-    direct = uni(segs <= 1.f && nb - fair <= over) != 0;
-    const float least = fmaxf(fminf(0.0625f * nb - 1.f, __builtin_amdgcn_sqrtf(1.25f * nb)), 4.f);
-    if (fair < least)
-      W2 = uni(min(W, nseg * (int)__builtin_ceilf((float)(int)C * __builtin_amdgcn_rcpf((float)nseg * least))));
-  }
+  for (int w = 0; w < kWaves; ++w) nbm = max(nbm, s_scan_max[w]);
+  constexpr SplitForm kForm = MULTI || PROMPT  ? kSplitGeneral
+                              : !Pol::kHalfPages ? kSplitFullPages
+                                                 : (D == 64 ? kSplitHalfPages64 : kSplitHalfPages128);
+  const Split cut = split_of(kForm, W, p.inv_ranges, nseg, (int)C, nbm);
+  const bool direct = uni(cut.whole) != 0;
+  const int W2 = uni(cut.shares);   // equal shares used
   // Never more shares than positions (C >= T >= Wn).  A share can still hold no
   // position when the shares are shorter than two costs.
   const int Wn = (int)min((int64_t)W2, T);
-  if (direct ? (int)blockIdx.x >= nseg : u >= Wn) return;
+  const int u = share_of_block(blockIdx.x, direct ? nseg : Wn);
+  if (u < 0) return;
 
   // 3. This workgroup's share [r0, r1) of the flattened (sequence, KV head, page)
   //    list, and this wave's quarter [w0, w1) of it.  Each wave walks its own pieces
@@ -1387,11 +1348,9 @@ void decode_attention_kernel(const Params p) {
   int w0, w1, wunit = 0;   // wunit: the unit of position w0 (when w0 < T)
   int64_t r0, r1;
   if (direct) {
-    // One segment, in page quarters.  Blocks 0 .. nseg - 1 work (every XCD has its
-    // part of them), contiguous runs of segments on one XCD as for the shares.
-    const int sg = xcd_contiguous(blockIdx.x, nseg);
-    wunit = sg / Hs;
-    const int gv = sg - wunit * Hs, pre = uni(s_pre[wunit]), nb = uni(s_pre[wunit + 1]) - pre;
+    // One segment, in page quarters.
+    wunit = u / Hs;
+    const int gv = u - wunit * Hs, pre = uni(s_pre[wunit]), nb = uni(s_pre[wunit + 1]) - pre;
     if constexpr (!MULTI && !PROMPT) {
       if (nb > 0) whole_segment<Pol>(p, wunit, gv, nb, uni(s_tail[wunit]), s_acc, s_ml);
       return;

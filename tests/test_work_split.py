@@ -1,0 +1,54 @@
+"""The kernel's rule for cutting a call's work (csrc/rlda_split.h), compiled for the host."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+import paper_2607_09207_amd as pkg
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(pkg.__file__)), "csrc")
+FORMS = {"full": 0, "half128": 1, "half64": 2, "general": 3}
+START = 2   # pages a segment's start costs
+
+
+class Split(ctypes.Structure):
+    _fields_ = [("whole", ctypes.c_bool), ("shares", ctypes.c_int)]
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("split")
+    (d / "rule.cpp").write_text('''#include "rlda_split.h"
+extern "C" rlda::Split split(int form, int W, int nseg, int cost, int nb) {
+  return rlda::split_of((rlda::SplitForm)form, W, 1.f / W, nseg, cost, nb);
+}
+extern "C" rlda::Split forced(int W, int nseg, int cost, int nb) {
+  return rlda::split_of(rlda::kSplitFullPages, W, 0.f, nseg, cost, nb);
+}
+extern "C" int share(int b, int n) { return rlda::share_of_block(b, n); }
+''')
+    so = str(d / "rule.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "rule.cpp"), "-o", so])
+    lib = ctypes.CDLL(so)
+    lib.split.restype = lib.forced.restype = Split
+    return lib
+
+
+def equal(rule, form, W, nseg, nb):
+    """The cut of nseg segments of nb pages."""
+    return rule.split(FORMS[form], W, nseg, nseg * (nb + START), nb)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 18, 29, 38, 116, 255, 256])
+def test_the_shares_in_use_are_spread_over_the_xcds(rule, n):
+    shares = [rule.share(b, n) for b in range(256)]
+    assert sorted(s for s in shares if s >= 0) == list(range(n))
+    per_xcd = [[s for s in shares[x::8] if s >= 0] for x in range(8)]
+    assert max(map(len, per_xcd)) - min(map(len, per_xcd)) <= 1
+    assert all(s == list(range(s[0], s[0] + len(s))) for s in per_xcd if s)   # neighbours on one XCD
+
+
+def test_a_forced_share_count_is_kept(rule):
+    s = rule.forced(7, 4, 40, 8)
+    assert not s.whole and s.shares == 7
