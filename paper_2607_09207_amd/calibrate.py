@@ -100,7 +100,7 @@ def work_split(seq_lens: Sequence[int], num_kv_heads: int, ranges: int, head_dim
     else:
         over = max(54 - 72 * segs, 26)
     whole = segs <= 1 and nb - fair <= over
-    least = max(min(nb / 16 - 1, (1.25 * nb) ** 0.5), 4)
+    least = max(min((nb + start_cost) / 16, (1.25 * nb) ** 0.5), 4)
     shares = int(ranges) if fair >= least else min(int(ranges), nseg * math.ceil(C / (nseg * least)))
     return whole, shares
 

@@ -56,10 +56,12 @@ struct Split {
 // half the workgroups are gone.  Multi-token, packed and prompt-state runs stream whole
 // segments through the general loop, which is slower a page.
 //   Equal shares hold at least 4 pages (one a wave), and so many that the largest
-// segment falls into about 16 pieces, one batch of its final merge; of longer segments
-// at least sqrt(1.25 nbmax), where pages and pieces cost alike (a share's page 0.15 us,
-// a piece 0.19 us).  12/2 heads, one sequence of 112 pages: 31.3 us in 256 shares, 13.5
-// so.  Where that bound holds the shares are a multiple of the segments, so that equal
+// segment falls into at most 16 pieces, one batch of its final merge (17, where lengths
+// differ and it begins inside a share); of segments above 300 pages at least
+// sqrt(1.25 nbmax), where pages and pieces cost alike (a share's page 0.15 us, a piece
+// 0.19 us).  us a call at d 128, one sequence of 64 / 112 / 188 pages: 8/1 heads bf16
+// 14.4 / - / 16.5 with nbmax / 16 - 1 (18 to 22 pieces) and 13.1 / - / 15.0 so; 12/2 fp8
+// - / 15.1 / - and - / 13.3 / - (12/2 bf16 in 256 shares 31.4).  Where that bound holds the shares are a multiple of the segments, so that equal
 // segments are cut alike.
 //   W workgroups (inv_ranges = 1 / W, or 0: the caller fixed the share count), nseg
 // segments costing `cost` together, the largest of nb_max pages.
@@ -70,7 +72,7 @@ RLDA_HD Split split_of(SplitForm form, int W, float inv_ranges, int nseg, int co
                      : form == kSplitFullPages ? __builtin_fmaxf(54.f - 72.f * segs, 26.f)
                                                : (form == kSplitHalfPages64 ? 78.f : 57.f) + __builtin_fmaxf(80.f * segs - 20.f, 0.f);
   Split s = {nseg <= W && nb - fair <= over, W};
-  const float least = __builtin_fmaxf(__builtin_fminf(0.0625f * nb - 1.f, split_sqrt(1.25f * nb)), 4.f);
+  const float least = __builtin_fmaxf(__builtin_fminf(0.0625f * (nb + (float)kStartCost), split_sqrt(1.25f * nb)), 4.f);
   if (fair < least) {
     const float n = (float)nseg * __builtin_ceilf((float)cost * split_rcp((float)nseg * least));
     s.shares = n < (float)W ? (int)n : W;

@@ -52,3 +52,16 @@ def test_the_shares_in_use_are_spread_over_the_xcds(rule, n):
 def test_a_forced_share_count_is_kept(rule):
     s = rule.forced(7, 4, 40, 8)
     assert not s.whole and s.shares == 7
+
+
+@pytest.mark.parametrize("nb", [1, 8, 62, 63, 64, 112, 188, 300, 310, 1000, 2048])
+@pytest.mark.parametrize("nseg", [1, 2, 3, 8, 13])
+def test_few_segments_fall_into_one_merge_batch(rule, nseg, nb):
+    """Alone, a segment is cut into at most 16 pieces, shares of at least 4 pages; above
+    300 pages into at most (nb + START) / sqrt(1.25 nb); a multiple of the segments."""
+    s = equal(rule, "full", 256, nseg, nb)
+    pieces = s.shares / nseg
+    if s.shares < 256:
+        assert pieces == int(pieces) >= 1
+        assert pieces <= max(16, -(-(nb + START) // (1.25 * nb) ** 0.5))
+        assert pieces == 1 or (nb + START) / (pieces - 1) >= 4
