@@ -40,21 +40,33 @@ struct Split {
 
 // calibrate.work_split mirrors it for plain calls.
 //   Whole segments: each workgroup takes one segment.  That skips the share search and
-// the hand-off of cut pieces (store, count, read back), about 5 us together, and its
-// waves stream (nbmax - fair) / 4 pages more than under equal shares of `fair` pages,
-// 0.4 to 0.6 us each while so few of them run.  us a call on batches of equal lengths,
-// equal shares against whole segments, 16 / 32 / 64 / 112 pages:
-//   28/4 bf16 d 128, B = 4:   13.2 / 13.9 / 14.6 / 15.4   against  8.1 / 9.7 / 15.8 / 26.7
-//                    B = 16:  11.2 / 12.4 / 14.3 / 17.5            8.2 / 10.3 / 17.7 / 28.7
-//                    B = 32:  12.3 / 14.3 / 18.7 / 25.9            8.4 / 11.7 / 19.7 / 31.5
-//   40/8 fp8 d 128,  B = 4:   14.2 / 14.5 / 14.9 / 15.5            7.4 / 9.5 / 14.3 / 21.5
-//                    B = 32:  12.9 / 15.1 / 20.0 / 27.5            7.7 / 10.0 / 15.0 / 22.4
-//   64/8 bf16 d 64,  B = 16:  10.9 / 12.3 / 14.4 / 17.7            6.5 / 8.2 / 12.2 / 18.3
-// (28/4, B = 60, 200 pages: 68.6 against 62.3).  `over` is where the two meet, in pages
-// over an equal share, by segments per workgroup: with one workgroup per CU whole
-// segments leave CUs idle that could read, with two (half-size pages) they don't until
-// half the workgroups are gone.  Multi-token, packed and prompt-state runs stream whole
-// segments through the general loop, which is slower a page.
+// the hand-off of cut pieces (store, count, read back), 3 to 5 us together, and its waves
+// stream (nbmax - fair) / 4 pages more than under equal shares of `fair` pages, 0.4 to
+// 0.6 us each while so few of them run.  us a call on batches of equal lengths, equal
+// shares against whole segments, 16 / 32 / 64 / 112 / 160 pages:
+//   28/4 bf16 d 128, B = 4:   11.8 / 12.8 / 14.7 / 15.5 / 16.2   against   8.0 / 9.9 / 14.7 / 21.8 / 31.2
+//                    B = 16:  11.2 / 12.1 / 13.9 / 16.7 / 20.3             8.1 / 10.2 / 17.6 / 27.9 / 38.5
+//                    B = 32:  12.0 / 13.6 / 18.1 / 25.4 / 32.9             8.2 / 11.6 / 19.4 / 31.1 / 42.4
+//                    B = 60:  15.1 / 19.1 / 28.4 / 42.2 / 55.6             8.9 / 13.0 / 22.5 / 36.7 / 50.7
+//   40/8 fp8 d 128,  B = 4:   11.3 / 13.0 / 14.6 / 15.6 / 16.6             7.5 / 9.6 / 14.6 / 21.5 / 28.6
+//                    B = 32:  12.9 / 15.2 / 20.1 / 27.8 / 36.0             7.6 / 9.9 / 15.0 / 22.6 / 30.4
+//   40/8 bf16 d 64,  B = 16:  10.9 / 12.2 / 14.4 / 17.8 / 21.5             6.5 / 8.1 / 12.2 / 18.2 / 24.6
+//                    B = 32:  12.1 / 14.3 / 18.9 / 26.5 / 34.0             6.7 / 8.7 / 13.5 / 21.1 / 28.4
+// `over` is where the two meet, in pages over an equal share, by segments per workgroup:
+// with one workgroup per CU whole segments leave CUs idle that could read, with two
+// (half-size pages) they don't until half the workgroups are gone.
+//   The general loop is slower a page, and slower again with the remainders that go with
+// a longer stream (rlda_kernels.hip), 8 / 16 / 32 / 48 / 64 pages:
+//   4 rows, 28/4 bf16 d 128, B = 4:   15.8 / 17.7 / 22.0 / 24.5 / 25.8    against   12.0 / 14.6 / 18.4 / 22.4 / 26.5
+//                            B = 16:  16.3 / 17.4 / 18.6 / 20.1 / 21.2              12.1 / 14.8 / 18.7 / 23.2 / 27.4
+//                            B = 32:  17.0 / 18.6 / 21.2 / 23.3 / 25.2              12.2 / 14.9 / 18.9 / 23.7 / 27.9
+//   3 rows, 40/8 fp8 d 128,  B = 8:   12.3 / 12.8 / 13.5 / 14.3 / 14.9              9.4 / 11.0 / 13.5 / 16.5 / 19.5
+//                            B = 24:  14.8 / 16.2 / 18.3 / 20.2 / 21.8              9.4 / 11.1 / 13.9 / 17.2 / 20.1
+//   after a prompt pass, 16/1 bf16 d 64, B = 16:   17.3 / 18.7 / 19.5 / 20.6 / 21.2   14.9 / 16.2 / 18.0 / 20.3 / 22.7
+//                                        B = 128:  19.0 / 19.5 / 20.7 / 22.1 / 22.8   15.9 / 17.5 / 19.6 / 22.2 / 24.4
+// There equal shares that are the segments anyway (all of one length, as many as
+// workgroups) cut nothing and stay without remainders: 4 rows, 40/8 fp8 d 128, B = 32,
+// 64 / 112 pages 23.6 / 32.5 against 27.4 / 39.8.
 //   Equal shares hold at least 4 pages (one a wave), and so many that the largest
 // segment falls into at most 16 pieces, one batch of its final merge (17, where lengths
 // differ and it begins inside a share); of segments above 300 pages at least
@@ -68,10 +80,11 @@ struct Split {
 RLDA_HD Split split_of(SplitForm form, int W, float inv_ranges, int nseg, int cost, int nb_max) {
   if (!(inv_ranges > 0.f)) return {false, W};
   const float nb = (float)nb_max, fair = (float)cost * inv_ranges, segs = (float)nseg * inv_ranges;
-  const float over = form == kSplitGeneral     ? __builtin_fmaxf(40.f - 48.f * segs, 20.f)
+  const float over = form == kSplitGeneral     ? __builtin_fmaxf(46.f - 96.f * segs, 20.f)
                      : form == kSplitFullPages ? __builtin_fmaxf(54.f - 72.f * segs, 26.f)
                                                : (form == kSplitHalfPages64 ? 78.f : 57.f) + __builtin_fmaxf(80.f * segs - 20.f, 0.f);
-  Split s = {nseg <= W && nb - fair <= over, W};
+  const bool aligned = nseg == W && cost == nseg * (nb_max + kStartCost);
+  Split s = {nseg <= W && nb - fair <= over && !(form == kSplitGeneral && aligned), W};
   const float least = __builtin_fmaxf(__builtin_fminf(0.0625f * (nb + (float)kStartCost), split_sqrt(1.25f * nb)), 4.f);
   if (fair < least) {
     const float n = (float)nseg * __builtin_ceilf((float)cost * split_rcp((float)nseg * least));

@@ -65,3 +65,26 @@ def test_few_segments_fall_into_one_merge_batch(rule, nseg, nb):
         assert pieces == int(pieces) >= 1
         assert pieces <= max(16, -(-(nb + START) // (1.25 * nb) ** 0.5))
         assert pieces == 1 or (nb + START) / (pieces - 1) >= 4
+
+
+@pytest.mark.parametrize("nb", [1, 64, 112])
+def test_shares_that_are_the_segments_stay_shares_in_the_general_loop(rule, nb):
+    """As many segments as workgroups, all of one length: cut nothing, gain nothing."""
+    s = equal(rule, "general", 256, 256, nb)
+    assert not s.whole and s.shares == 256
+    assert rule.split(FORMS["general"], 256, 256, 256 * (nb + START) - 1, nb).whole   # one page less in one of them
+    assert equal(rule, "general", 256, 255, nb).whole
+    assert equal(rule, "full", 256, 256, nb).whole
+
+
+# (form, segments of 256 workgroups, pages over an equal share that still go whole)
+LINES = [("full", 4, 52.875), ("full", 128, 26), ("full", 256, 26), ("half128", 32, 57), ("half128", 128, 77),
+         ("half64", 32, 78), ("half64", 256, 138), ("general", 16, 40), ("general", 64, 22), ("general", 255, 20)]
+
+
+@pytest.mark.parametrize("form,nseg,over", LINES)
+def test_both_sides_of_each_line(rule, form, nseg, over):
+    W = 256
+    whole = [nb for nb in range(1, 2000) if rule.split(FORMS[form], W, nseg, 256 * 40, nb).whole]
+    assert whole == list(range(1, 1 + int(over + 40)))   # the equal share is 40 pages
+    assert not rule.split(FORMS[form], W, W + 1, (W + 1) * 3, 1).whole
