@@ -1923,7 +1923,8 @@ void prompt_kernel(const Params p) {
 }
 
 // ---------------------------------------------------------------- KV append
-// One wave per (sequence, KV head) and cache (K or V): lane l owns elements
+// One wave per (sequence, KV head) and cache (K or V; one wave for both where they are the
+// same memory, since each reads and rewrites the page): lane l owns elements
 // [l * E, (l + 1) * E) of the new row, E = D / 64.  bf16 / fp32 caches copy the row into
 // its slot.  fp8 caches keep the page's scale covering every row written so far: the
 // first row of a page sets amax / 448; a later row with a larger amax raises the scale
@@ -1937,15 +1938,11 @@ __device__ __forceinline__ uint32_t e4m3x2(float a, float b) {
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false) & 0xFFFFu;
 }
 
+// One sequence, KV head and cache.
 template <int D, KvKind KIND>
-__global__ __launch_bounds__(kThreads) void append_kernel(const Params p) {
+__device__ __forceinline__ void append_row(const Params& p, int item, bool is_v, int lane) {
   constexpr int E = D / 64;
-  const int lane = threadIdx.x & 63;
-  const int wave = uni((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
-  const int item = wave >> 1;
-  if (item >= p.batch * p.num_kv_heads) return;
   const int b = item / p.num_kv_heads, g = item - b * p.num_kv_heads;
-  const bool is_v = wave & 1;
   char* cache = (char*)(is_v ? p.v : p.k);
   const void* in = is_v ? p.v_in : p.k_in;
   typedef typename std::conditional<KIND == KvKind::F32, float, uint16_t>::type Elem;
@@ -2009,6 +2006,24 @@ __global__ __launch_bounds__(kThreads) void append_kernel(const Params p) {
     else
       *dst = (uint8_t)(s_new > 0.f ? e4m3x2(v[0] / s_new, 0.f) & 0xFFu : 0u);
     if (lane == 0) *scale = s_new;
+  }
+}
+
+template <int D, KvKind KIND>
+__global__ __launch_bounds__(kThreads) void append_kernel(const Params p) {
+  const int lane = threadIdx.x & 63;
+  const int wave = uni((int)(blockIdx.x * kWaves + (threadIdx.x >> 6)));
+  const int item = wave >> 1;
+  if (item >= p.batch * p.num_kv_heads) return;
+  const bool is_v = wave & 1;
+  // One cache (or one scale array) given as both: K, then V, in one wave.
+  const bool one = p.k == p.v || (KIND == KvKind::FP8 && p.k_scale == p.v_scale);
+  if (one && is_v) return;
+  append_row<D, KIND>(p, item, is_v, lane);
+  if (one) {
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    append_row<D, KIND>(p, item, true, lane);
   }
 }
 

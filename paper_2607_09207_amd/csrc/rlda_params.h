@@ -107,7 +107,7 @@ int launch_grouped(KvKind kind, int head_dim, int group, const Params& p, int ng
 // two waves per SIMD; batch <= kTwoWgMaxBatch, nranges twice the CUs): eight waves
 // per CU keep twice the tiles in flight.
 int launch_decode_two(KvKind kind, int head_dim, const Params& p, void* stream, void* ev_begin, void* ev_end);
-// KV append: one wave per (sequence, KV head).
+// KV append: one wave per (sequence, KV head) and cache; one for both where they are one.
 int launch_append(KvKind kind, int head_dim, const Params& p, void* stream);
 // Device address of the static scratch on the current device (kScratchBytes bytes),
 // looked up once per device; 0 on success.

@@ -164,3 +164,26 @@ def test_append_contract_violations_raise_flags_and_write_nothing_else(torch_cud
     # only sequence 0's slot changed
     diff = np.argwhere(np.any(kc != w.k_cache, axis=-1))
     assert {tuple(r) for r in diff.tolist()} <= {(int(w.block_table[0, 0]), g, 4) for g in range(2)}
+
+
+@pytest.mark.parametrize("kv,d", [("bf16", 128), ("f32", 64), ("fp8_e4m3fn", 128), ("fp8_e4m3fn", 64)])
+def test_one_cache_given_as_both_takes_k_then_v(torch_cuda, kv, d):
+    """K and V in the same memory (caches and scales): every row is K's, then V's over it,
+    also where both raise the page's scale."""
+    torch = torch_cuda
+    rng = np.random.default_rng(31)
+    w = I.make_custom([1, 2, 16, 17, 40, 300, 31], 8, 4, d, q_dtype="f32" if kv == "f32" else "bf16", kv_dtype=kv, seed=31)
+    w = dataclasses.replace(w, v_cache=w.k_cache.copy(), v_scale=None if w.k_scale is None else w.k_scale.copy())
+    kn, vn = new_rows(w, rng, mags=[1, 4, 1, 9, 0.1, 20, 3])
+    k1, _, s1, _ = OA.append(w, kn, vn)
+    want = OA.append(dataclasses.replace(w, v_cache=k1, v_scale=s1), kn, vn)
+    t = I.to_torch(w, "cuda")
+    to = lambda x: (torch.from_numpy(x) if kv == "f32" else torch.from_numpy(x.view(np.int16)).view(torch.bfloat16)).cuda()
+    h = handle_for(w)
+    h.append(to(kn), to(vn), t["k_cache"], t["k_cache"], t["block_table"], t["seq_lens"], k_scale=t["k_scale"],
+             v_scale=t["k_scale"])
+    torch.cuda.synchronize()
+    got = t["k_cache"].contiguous().view(torch.uint8).cpu().numpy()
+    assert np.array_equal(got.ravel(), np.ascontiguousarray(want[1]).view(np.uint8).ravel())
+    if w.k_scale is not None:
+        assert np.array_equal(t["k_scale"].cpu().numpy().view(np.uint32), want[3].view(np.uint32))
