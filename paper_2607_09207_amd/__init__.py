@@ -82,10 +82,11 @@ class DecodeAttention:
         self.grouped_workspace_bytes = int(n.value)
         self._ws = {}
         # The native call path (csrc/fastcall.cpp); it shares the workspaces by device.
-        self._fast = _abi.fastcall().Layer(h.value, self._ws, (num_q_heads, num_kv_heads, head_dim, page_size, max_batch,
-                                                               max_pages_per_seq),
-                                           (cfg.q_dtype, cfg.kv_dtype, cfg.out_dtype), self._kv_strides,
-                                           self.workspace_bytes + 256, self.grouped_workspace_bytes + 256)
+        native = _abi.fastcall()
+        self._fast = _abi.LEFT_TO_PYTHON if native is None else native.Layer(
+            h.value, self._ws, (num_q_heads, num_kv_heads, head_dim, page_size, max_batch, max_pages_per_seq),
+            (cfg.q_dtype, cfg.kv_dtype, cfg.out_dtype), self._kv_strides, self.workspace_bytes + 256,
+            self.grouped_workspace_bytes + 256)
 
     def __del__(self):
         h = getattr(self, "_h", None)

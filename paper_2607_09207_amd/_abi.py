@@ -86,9 +86,21 @@ def load() -> ctypes.CDLL:
 _fast = None
 
 
+class LeftToPython:
+    """Stands in for the native call path and takes no call."""
+
+    def run(self, *args):
+        return None
+
+    grouped = multi = noalloc = append = run
+
+
+LEFT_TO_PYTHON = LeftToPython()
+
+
 def fastcall():
-    """The native call path (csrc/fastcall.cpp), bound to the loaded library; raises if it
-    has not been built."""
+    """The native call path (csrc/fastcall.cpp), bound to the loaded library, or None, with
+    a warning, where it is not built or does not load: the Python path takes every call."""
     global _fast
     lib = load()
     if _fast is None or _fast[0] is not lib:
@@ -96,8 +108,12 @@ def fastcall():
         try:
             from . import _fastcall
         except ImportError as e:
-            raise ImportError("the native call path is missing or does not load: build it with "
-                              f"__graft_entry__.build() or python -m paper_2607_09207_amd.build ({e})") from e
+            import warnings
+            warnings.warn(f"the native call path is missing or does not load ({e}); calls take about 12 us more on the "
+                          "host.  Build it with __graft_entry__.build() or python -m paper_2607_09207_amd.build",
+                          RuntimeWarning, stacklevel=3)
+            _fast = (lib, None)
+            return None
         # CPU-only torch builds have no stream lookup; every call is then left to Python.
         raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         addr = [ctypes.cast(getattr(lib, "rl_decode_attn_" + n), ctypes.c_void_p).value

@@ -38,3 +38,23 @@ def test_errors_are_those_of_the_python_checks():
                  lambda: h.append(q[:, :2].contiguous(), q[:, :2].contiguous(), k, v, bt, sl)):
         with pytest.raises(RldaError, match="must be on a GPU"):
             call()
+
+
+def test_without_the_native_path_the_python_path_takes_every_call(monkeypatch):
+    import sys
+
+    import paper_2607_09207_amd as pkg
+    from paper_2607_09207_amd import _abi
+    monkeypatch.setattr(_abi, "_fast", None)
+    monkeypatch.delattr(pkg, "_fastcall", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2607_09207_amd._fastcall", None)   # the import fails
+    with pytest.warns(RuntimeWarning, match="native call path"):
+        h = layer()
+    layer()   # warned once
+    q, k, v, bt, sl = args()
+    for call in (lambda: h(q, k, v, bt, sl), lambda: h.run_noalloc(q, k, v, bt, sl),
+                 lambda: h(q, k, v, bt, sl, group_size=2, prefix_pages=sl),
+                 lambda: h.multi(q, k, v, bt, sl, torch.zeros(3, dtype=torch.int32)),
+                 lambda: h.append(q[:, :2].contiguous(), q[:, :2].contiguous(), k, v, bt, sl)):
+        with pytest.raises(RldaError, match="must be on a GPU"):
+            call()
