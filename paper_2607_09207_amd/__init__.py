@@ -91,6 +91,7 @@ class DecodeAttention:
     def __del__(self):
         h = getattr(self, "_h", None)
         if h is not None and h.value:
+            self._fast = _abi.LEFT_TO_PYTHON   # it holds the handle's address
             self._lib.rl_decode_attn_destroy(h)
             self._h = None
 

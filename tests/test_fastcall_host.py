@@ -58,3 +58,11 @@ def test_without_the_native_path_the_python_path_takes_every_call(monkeypatch):
                  lambda: h.append(q[:, :2].contiguous(), q[:, :2].contiguous(), k, v, bt, sl)):
         with pytest.raises(RldaError, match="must be on a GPU"):
             call()
+
+
+def test_a_destroyed_layer_keeps_no_handle_in_the_native_path():
+    from paper_2607_09207_amd import _abi
+    h = layer()
+    assert isinstance(h._fast, _abi.fastcall().Layer)
+    h.__del__()
+    assert h._h is None and h._fast is _abi.LEFT_TO_PYTHON
