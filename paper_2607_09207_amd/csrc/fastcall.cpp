@@ -137,7 +137,13 @@ bool common(const Layer* L, Call& c, PyObject* const* a, int dev, int64_t batch)
       return false;
     }
   } else if (!as_int(a[6], 0, &s)) {
-    return false;
+    PyObject* r = PyObject_GetAttrString(a[6], "cuda_stream");   // a torch.cuda.Stream
+    const bool ok = r && as_int(r, 0, &s);
+    Py_XDECREF(r);
+    if (!ok) {
+      PyErr_Clear();
+      return false;
+    }
   }
   c.stream = (void*)(intptr_t)s;
   return true;

@@ -86,6 +86,33 @@ def test_native_path_is_the_python_path(torch_cuda, kv, layout, given):
     torch.cuda.synchronize()
 
 
+def test_a_stream_object_is_taken_and_used(torch_cuda):
+    torch = torch_cuda
+    w = I.make_custom([40, 300, 20], 8, 2, 128, seed=18)
+    t = I.to_torch(w, "cuda")
+    h = handle_for(w)
+    h.workspace(t["q"].device)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    fn = lambda: h(t["q"], t["k_cache"], t["v_cache"], t["block_table"], t["seq_lens"], stream=side)
+
+    def on_side():
+        o = fn()
+        side.synchronize()
+        return o.clone()
+
+    a, b = both(h, on_side)
+    assert torch.equal(a, b)
+    # work queued on the side stream first holds the call back, work on the current one does not
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(2_000_000)
+    done = torch.cuda.Event()
+    fn()
+    done.record(side)
+    assert not done.query()
+    side.synchronize()
+
+
 def test_what_the_python_checks_refuse_is_refused(torch_cuda):
     torch = torch_cuda
     w = I.make_custom([40, 300, 20], 8, 2, 128, seed=16)
