@@ -537,8 +537,7 @@ rlda_status rl_decode_attn_run_multi(rl_decode_attn_t h, int32_t batch, int32_t 
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return RLDA_ERR_HIP;
   p.nranges = cu_count(dev);
-  const bool small =
-      batch <= rlda::kMultiSmallMaxBatch && blocks_of(rlda::kMultiRows) * c.num_kv_heads <= p.nranges;
+  const bool small = rlda::kMultiSplits && blocks_of(rlda::kMultiRows) * c.num_kv_heads <= p.nranges;
   const int64_t blocks = blocks_of(small ? rlda::kMultiSmallRows : rlda::kMultiRows);
   // Four KV heads: each XCD takes one KV head of one of two sequence classes, and
   // the grid holds 8 blocks per row block so that either class fits (see the kernel).

@@ -51,10 +51,7 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 #endif
 constexpr int kTile = 32;                     // rows (and keys) of one MFMA tile
 constexpr int kNT = kMultiTiles;              // 32-row tiles per wave
-#ifndef RLDA_MQ_KEY_TILES
-#define RLDA_MQ_KEY_TILES 1                   // 32-key score tiles per key block
-#endif
-constexpr int kKH = RLDA_MQ_KEY_TILES;
+constexpr int kKH = kMultiKeyTiles;           // 32-key score tiles per key block
 constexpr int kKeys = kTile * kKH;            // keys per block (2 kKH pages)
 
 #ifndef RLDA_MQ_WAVES_D64
@@ -685,7 +682,7 @@ void multi_query_kernel(const Params p) {
     // Wave w computes blocks w, w + 4, .. of the workgroup's one row tile, each staged
     // through registers into the wave's own buffer: no barrier.  The next block's pages
     // are loaded while a block is computed.
-    static_assert(kNT == 1 && kKH == 1, "one row tile, two pages a block");
+    static_assert(!SMALL || kMultiSplits, "one row tile, two pages a block");
     // Page ids come 32 blocks of the wave at a time: lane 2k + h, page h of its k-th.
     Staged sk[2], sv[2];
     int ids = 0;
@@ -869,11 +866,12 @@ int launch_multi_t(const Params& p, int grid, void* stream, void* ev_begin, void
 int launch_multi(KvKind kind, int head_dim, bool small, const Params& p, int grid, void* stream, void* ev_begin,
                  void* ev_end) {
   if (kind != KvKind::BF16 && kind != KvKind::FP8) return -1;
+  constexpr bool S = kMultiSplits;
   auto* const launch = kind == KvKind::BF16
-                           ? (head_dim == 128 ? (small ? launch_multi_t<128, false, true> : launch_multi_t<128, false, false>)
-                                              : (small ? launch_multi_t<64, false, true> : launch_multi_t<64, false, false>))
-                           : (head_dim == 128 ? (small ? launch_multi_t<128, true, true> : launch_multi_t<128, true, false>)
-                                              : (small ? launch_multi_t<64, true, true> : launch_multi_t<64, true, false>));
+                           ? (head_dim == 128 ? (small ? launch_multi_t<128, false, S> : launch_multi_t<128, false, false>)
+                                              : (small ? launch_multi_t<64, false, S> : launch_multi_t<64, false, false>))
+                           : (head_dim == 128 ? (small ? launch_multi_t<128, true, S> : launch_multi_t<128, true, false>)
+                                              : (small ? launch_multi_t<64, true, S> : launch_multi_t<64, true, false>));
   return launch(p, grid, stream, ev_begin, ev_end);
 }
 

@@ -113,8 +113,8 @@ int launch_append(KvKind kind, int head_dim, const Params& p, void* stream);
 // looked up once per device; 0 on success.
 int noalloc_scratch(void** ptr);
 // Multi-token queries (rlda_multi.hip): one workgroup per (128-row query block, KV head).
-// `small` (batch <= kMultiSmallMaxBatch): the grid has one per (32-row block, KV head), and
-// the kernel takes either size of block, 32 rows with the keys split over the waves.
+// `small` (kMultiSplits only): the grid has one per (32-row block, KV head), and the kernel
+// takes either size of block, 32 rows with the keys split over the waves.
 int launch_multi(KvKind kind, int head_dim, bool small, const Params& p, int grid, void* stream, void* ev_begin,
                  void* ev_end);
 // Multi-token queries with at most 16 * tiles rows per (sequence, KV head) segment
@@ -130,10 +130,14 @@ int launch_decode_packed(KvKind kind, int head_dim, int tiles, const Params& p, 
 #define RLDA_MQ_TILES 1            // 32-row MFMA tiles per wave in the multi-token kernel
 #endif
 constexpr int kMultiTiles = RLDA_MQ_TILES;
+#ifndef RLDA_MQ_KEY_TILES
+#define RLDA_MQ_KEY_TILES 1        // 32-key score tiles per key block of it
+#endif
+constexpr int kMultiKeyTiles = RLDA_MQ_KEY_TILES;
 constexpr int kMultiRowsLog2 = kMultiTiles == 1 ? 7 : 8;
 constexpr int kMultiRows = 1 << kMultiRowsLog2;   // query rows (token, head pairs) per workgroup of the multi-token kernel
 constexpr int kMultiSmallRows = 32;      // ... with the keys split over its waves
-constexpr int kMultiSmallMaxBatch = 512;
+constexpr bool kMultiSplits = kMultiTiles == 1 && kMultiKeyTiles == 1;   // the form that is built for that
 constexpr int kMultiMaxBatch = 4096;   // its per-sequence LDS tables stay within 48 KiB of LDS per workgroup
 constexpr int kPackMaxBatch = 4096;    // packed grouped runs: per-sequence and per-pack LDS tables of this size
 constexpr int kPackMaxMembers = 7;     // ... members per pack (3 bits of the page descriptor, 7 = every member)
