@@ -1409,13 +1409,17 @@ void decode_attention_kernel(const Params p) {
     // flight, the compiler has to take them for the newest loads wherever an id may be
     // read, and waits for every page in flight before each issue: one page ahead is what
     // then remains.  us a call, left in flight / waited for:
-    //   four sequences of 8k-16k tokens 31.4 / 30.3, long-tailed bf16 78.0 / 77.3, after
-    //   the prompt pass 119.8 / 118.7, verification 92.3 / 91.2 (fp8 82.4 / 80.3), packed
-    //   groups at d = 64 91.6 / 84.1 and 25.6 / 24.4;
-    //   two workgroups per CU (fp8 long-tailed 223.4 / 228.1, d = 64 43.8 / 44.3), the
-    //   fp32 stream (11.6 / 11.8) and packed groups at d = 128 (79.7 / 80.1) have enough
-    //   in flight with one page ahead, and more of them at once costs bandwidth.
-    constexpr bool kIdsWaited = WPE == 1 && Pol::kQRing && !(PACK && D == 128);
+    //   verification of 64 long-tailed sequences, 40/8 heads: bf16 d 128 106.7 / 105.7, d 64
+    //   70.3 / 60.2, fp8 75.7 / 63.8 and 62.7 / 49.8; after the prompt pass, 16/1: 76.2 /
+    //   76.2, 49.6 / 45.9, 69.2 / 66.0 and 47.4 / 45.1; plain, 600 sequences, 8/1: 125.5 /
+    //   124.5, 83.3 / 70.1, 89.2 / 73.7 and 72.7 / 56.2; packed groups of 8, bf16 d 64, 12/2:
+    //   35.9 / 33.0 and 24.3 / 22.5.
+    //   Left in flight, since one page ahead is enough and more at once cost bandwidth: two
+    //   workgroups per CU (fp8 long-tailed 224.2 / 229.1), packed groups of fp8 (the same, d
+    //   128 39.2 / 41.4 and 26.6 / 27.5, d 64 32.9 / 34.8, prompts of 4096 79.2 / 85.0) and
+    //   the fp32 stream (31.2 / 31.6 and 24.1 / 24.3); packed bf16 at d 128 is the same
+    //   either way (47.4 / 47.3, 30.1 / 29.7, 50.1 / 50.5, 80.6 / 80.9).
+    constexpr bool kIdsWaited = WPE == 1 && Pol::kQRing && (!PACK || (D == 64 && !Pol::kFp8));
     const int cn = w1 - w0;   // positions of this quarter (relative index k)
     // The unit of a chunk's last position bounds the units of the next chunk from below.
     auto unit_of_info = [](int info) { return (info >> kInfoSeqShift) & (PACK ? 4095 : 8191); };
