@@ -129,6 +129,26 @@ def test_what_the_python_checks_refuse_is_refused(torch_cuda):
         assert e.value.status == -1
     with pytest.raises(RldaError):
         h(q, k, v, bt, sl, num_pages=k.shape[0] + 1)
+    i32 = lambda n: torch.zeros(n, dtype=torch.int32, device="cuda")
+    qs = torch.arange(4, dtype=torch.int32, device="cuda")
+    new = torch.zeros((3, 2, 128), dtype=q.dtype, device="cuda")
+    h.workspace(q.device, grouped=True)
+    for call in (lambda: h(q, k, v, bt, sl, group_size=2, prefix_pages=i32(1)),            # two groups
+                 lambda: h(q, k, v, bt, sl, group_size=2, prefix_pages=i32(2).long()),
+                 lambda: h(q, k, v, bt, sl, group_size=2),
+                 lambda: h(q, k, v, bt, sl, group_size=0, prefix_pages=i32(2)),
+                 lambda: h.multi(q, k, v, bt, sl, qs.long()),
+                 lambda: h.multi(q, k, v, bt, sl, qs[:3]),
+                 lambda: h.multi(q.float(), k, v, bt, sl, qs),
+                 lambda: h.append(new, new[:, :1], k, v, bt, sl),
+                 lambda: h.append(new.float(), new, k, v, bt, sl),
+                 lambda: h.append(new, new, k, v, bt[:, :1], sl),
+                 lambda: h.run_noalloc(q, k, v, bt, sl, flags=i32(2)),
+                 lambda: h.run_noalloc(q, k, v, bt, sl, flags=i32(1).long()),
+                 lambda: h.run_noalloc(q, k, v, bt, sl, out=torch.empty(q.shape, dtype=q.dtype, device="cuda"))):
+        with pytest.raises(RldaError) as e:
+            call()
+        assert e.value.status == -1
     with pytest.raises(RldaError) as e:   # too small a workspace: the library's own check
         h(q, k, v, bt, sl, workspace=torch.zeros(512, dtype=torch.uint8, device="cuda"))
     assert e.value.status == -4

@@ -28,7 +28,7 @@ CASES = {
     "few_pages_fp8": ("fp8_e4m3fn", 40, 8, 128, [1, 16, 17, 0, 64, 65, 81]),
     "few_pages_d64": ("bf16", 16, 16, 64, [1, 15, 49, 256, 0, 257]),
     "few_pages_f32": ("f32", 4, 2, 64, [1, 16, 17, 0, 64, 65, 250]),
-    # every workgroup has a segment (256 of them), and one sequence more than that
+    # a segment for each workgroup (two a CU at d = 64: 512), and more segments than those
     "all_workgroups_bf16": ("bf16", 8, 8, 64, [40 + 7 * i for i in range(64)]),
     "more_segments_than_workgroups": ("bf16", 16, 16, 128, [20 + 3 * i for i in range(17)]),
     # more than 64 pages to a wave: equal long segments on three quarters of the workgroups
@@ -83,6 +83,32 @@ def test_whole_segments_keep_the_probabilities_remainders(torch_cuda, name):
     assert flags == 0
     worst = float(np.max(np.abs(got - oracle.run(w))))
     assert worst <= 2.0 ** -16 * 6.0, worst   # |v| < 6: normal values
+
+
+# As many segments as workgroups on 256 CUs, and one more: (dtype, d, KV heads, sequences).
+EDGE = {"full_256": ("bf16", 128, 1, 256), "full_257": ("bf16", 128, 1, 257),
+        "half_512": ("bf16", 64, 2, 256), "half_513": ("bf16", 64, 3, 171),
+        "fp8_512": ("fp8_e4m3fn", 128, 2, 256), "fp8_513": ("fp8_e4m3fn", 128, 3, 171)}
+
+
+@pytest.mark.parametrize("name", list(EDGE))
+def test_as_many_segments_as_workgroups_and_one_more(torch_cuda, name):
+    """Whole segments up to there, W equal shares (no remainders) above: the error tells."""
+    from paper_2607_09207_amd import calibrate
+    cus = torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    if cus != 256:
+        pytest.skip("the sequence counts are for 256 CUs")
+    kv, d, hkv, n = EDGE[name]
+    w = I.make_custom([40 + i % 60 for i in range(n)], 4 * hkv, hkv, d, kv_dtype=kv, seed=77, extra_pages=2)
+    workgroups = cus if name.startswith("full") else 2 * cus
+    whole, shares = calibrate.work_split(w.seq_lens, hkv, workgroups, d, kv)
+    assert (whole, shares) == ((True, shares) if n * hkv <= workgroups else (False, workgroups))
+    got, flags = gpu_run(torch_cuda, w, tag=f"edge {name}")
+    assert flags == 0
+    want = oracle.run(w)
+    assert_close(got, want, kv, f"edge {name}")
+    worst = float(np.max(np.abs(got - want)))
+    assert (worst <= 2.0 ** -16 * 6.0) == whole, worst
 
 
 # The other calls that get longer streams than one equal share a workgroup: rows of several
