@@ -85,35 +85,45 @@ def max_pieces(seq_lens: Sequence[int], num_kv_heads: int, ranges: int, page: in
     return int(np.max(own(c1) - own(c0) + 1))
 
 
+def half_pages(kv_dtype: str, head_dim: int) -> bool:
+    """Caches whose plain calls run two workgroups per CU (up to 512 sequences)."""
+    return kv_dtype == "fp8_e4m3fn" or (kv_dtype == "bf16" and head_dim == 64)
+
+
 def work_split(seq_lens: Sequence[int], num_kv_heads: int, ranges: int, head_dim: int, kv_dtype: str,
-               page: int = 16, start_cost: int = START_COST):
-    """(whole, shares) of a decode call on a handle without a forced share count: whether
-    each (sequence, KV head) segment goes whole to one workgroup, and otherwise how many
-    equal shares the kernel cuts the list into (its arithmetic is fp32; a call that lies
-    within rounding of a line may go the other way here)."""
+               page: int = 16, start_cost: int = START_COST, max_pages: int = 0):
+    """(whole, shares) of a plain decode call on a handle without a forced share count:
+    whether each (sequence, KV head) segment goes whole to one workgroup, and otherwise how
+    many equal shares the kernel cuts the list into (the rule of csrc/rlda_split.h, there in
+    fp32: a call that lies within rounding of a line may go the other way here).  `ranges`
+    workgroups, at most one per page that a table of `max_pages` (0: any) could name."""
     n = (np.maximum(np.asarray(seq_lens, np.int64), 0) + page - 1) // page
     nseg, nb = len(n) * int(num_kv_heads), float(n.max(initial=0))
+    if max_pages > 0:
+        ranges = min(int(ranges), nseg * int(max_pages))
     C = float(num_kv_heads) * float(n.sum() + start_cost * np.count_nonzero(n))
     fair, segs = C / ranges, nseg / ranges
-    if kv_dtype == "fp8_e4m3fn" or (kv_dtype == "bf16" and head_dim == 64):   # half-size pages
+    if half_pages(kv_dtype, head_dim):
         over = (78 if head_dim == 64 else 57) + max(80 * segs - 20, 0)
     else:
         over = max(54 - 72 * segs, 26)
-    whole = segs <= 1 and nb - fair <= over
+    whole = nseg <= ranges and nb - fair <= over
     least = max(min((nb + start_cost) / 16, (1.25 * nb) ** 0.5), 4)
     shares = int(ranges) if fair >= least else min(int(ranges), nseg * math.ceil(C / (nseg * least)))
     return whole, shares
 
 
 def features_ext(seq_lens: Sequence[int], num_kv_heads: int, ranges: int, head_dim: int = 0,
-                 kv_dtype: str = "") -> np.ndarray:
+                 kv_dtype: str = "", max_pages: int = 0) -> np.ndarray:
     """(W, N_tok, H, largest piece count of a segment) of one call.  With head_dim and
     kv_dtype: on a handle that leaves the choice of shares to the kernel, `ranges`
-    workgroups at one per CU; without: cut into `ranges` equal shares."""
+    workgroups at one per CU (block tables of max_pages); without: cut into `ranges` equal
+    shares."""
     whole, shares = False, int(ranges)
     if head_dim:
-        two = (kv_dtype == "fp8_e4m3fn" or (kv_dtype == "bf16" and head_dim == 64)) and len(seq_lens) <= 512
-        whole, shares = work_split(seq_lens, num_kv_heads, 2 * ranges if two else ranges, head_dim, kv_dtype)
+        two = half_pages(kv_dtype, head_dim) and len(seq_lens) <= 512
+        whole, shares = work_split(seq_lens, num_kv_heads, 2 * ranges if two else ranges, head_dim, kv_dtype,
+                                   max_pages=max_pages)
     pieces = 1 if whole else max_pieces(seq_lens, num_kv_heads, shares)
     return np.concatenate([features(seq_lens), [float(pieces)]])
 
@@ -232,7 +242,8 @@ def calibrate(cfg, torch, dev, train_seeds=(1,), test_seeds=(2,), log=print) -> 
         for s in seeds:
             for lens in batch_plan(s, cfg):
                 t = measure(cfg, lens, torch, dev)
-                rows[split].append((features_ext(lens, cfg[2], ranges, cfg[3], cfg[5]), t))
+                pages = (int(lens.max()) + 15) // 16
+                rows[split].append((features_ext(lens, cfg[2], ranges, cfg[3], cfg[5], pages), t))
                 log(f"[calibrate] {cfg[0]} {split} seed={s} B={len(lens)} H={int(lens.sum())} "
                     f"pieces={int(rows[split][-1][0][3])} t={t * 1e6:.1f} us")
     Xtr = np.array([r[0] for r in rows["train"]]); ytr = np.array([r[1] for r in rows["train"]])

@@ -3,9 +3,11 @@ import ctypes
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 import paper_2607_09207_amd as pkg
+from paper_2607_09207_amd import calibrate as C
 
 CSRC = os.path.join(os.path.dirname(os.path.abspath(pkg.__file__)), "csrc")
 FORMS = {"full": 0, "half128": 1, "half64": 2, "general": 3}
@@ -88,3 +90,32 @@ def test_both_sides_of_each_line(rule, form, nseg, over):
     whole = [nb for nb in range(1, 2000) if rule.split(FORMS[form], W, nseg, 256 * 40, nb).whole]
     assert whole == list(range(1, 1 + int(over + 40)))   # the equal share is 40 pages
     assert not rule.split(FORMS[form], W, W + 1, (W + 1) * 3, 1).whole
+
+
+@pytest.mark.parametrize("form,kv,d", [("full", "bf16", 128), ("half128", "fp8_e4m3fn", 128), ("half64", "bf16", 64),
+                                       ("half64", "fp8_e4m3fn", 64), ("full", "f32", 64)])
+def test_the_predictor_mirrors_the_rule(rule, form, kv, d):
+    rng = np.random.default_rng(5)
+    differ = 0
+    for _ in range(3000):
+        hkv, W = int(rng.integers(1, 9)), int(rng.choice([64, 256, 512]))
+        lens = np.exp(rng.uniform(0, np.log(20000), int(rng.integers(1, 80)))).astype(int) * (rng.random() < 0.98)
+        n = (lens + 15) // 16
+        cost = hkv * int(n.sum() + START * np.count_nonzero(n))
+        got = rule.split(FORMS[form], W, len(lens) * hkv, cost, int(n.max()))
+        whole, shares = C.work_split(lens, hkv, W, d, kv)
+        differ += (got.whole, got.shares) != (whole, shares)
+    assert differ <= 3   # fp32 against float64, within rounding of a line
+
+
+def test_a_small_table_bounds_the_workgroups():
+    """One page a sequence: no more workgroups than pages, as the host launches."""
+    assert C.work_split([5] * 3, 2, 256, 128, "bf16", max_pages=1) == C.work_split([5] * 3, 2, 6, 128, "bf16")
+    assert C.work_split([500], 1, 256, 128, "bf16", max_pages=32) == C.work_split([500], 1, 32, 128, "bf16")
+    assert C.work_split([500], 1, 256, 128, "bf16", max_pages=1000) == C.work_split([500], 1, 256, 128, "bf16")
+
+
+def test_pieces_of_the_chosen_cut():
+    assert C.features_ext([500] * 4, 4, 256, 128, "bf16")[3] == 1           # whole segments
+    assert C.features_ext([3000], 1, 256, 128, "bf16")[3] == 16             # one segment alone
+    assert C.features_ext([3000], 1, 256)[3] == C.max_pieces([3000], 1, 256) > 100   # 256 shares
