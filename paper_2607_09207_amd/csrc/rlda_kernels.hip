@@ -15,10 +15,10 @@
 //   2. Page gather.  Each of the 4 waves of a workgroup takes a quarter of the
 //      share and walks it as one continuous stream of pages: its lanes decode 64
 //      positions at a time (sequence, KV head, page id, valid tokens, segment
-//      start/end flags) one chunk ahead of use, and the wave keeps 3 pages in
-//      flight in registers with buffer loads whose range check returns zero past
-//      a page's last valid token, so masked slots cost no memory traffic and
-//      never yield NaN.  A segment's Q operand is loaded with its first page.
+//      start/end flags) one chunk ahead of use, and the wave computes one page
+//      while the two after it are in flight to registers, by buffer loads whose
+//      range check returns zero past a page's last valid token, so masked slots
+//      cost no memory traffic and never yield NaN.  A segment's Q operand is loaded with its first page.
 //      Segment boundaries inside the stream cost no pipeline restart.
 //   3. Scores and softmax.  All G query heads that share the KV head are packed
 //      into one 16-row MFMA tile: S^T = K Q^T with v_mfma_f32_16x16x32_bf16; the
@@ -27,7 +27,9 @@
 //      score exceeds it by more than 8, i.e. a probability above 2^8.
 //   4. PV.  O^T += V^T P^T with v_mfma_f32_16x16x16_bf16: the score tile's output
 //      registers are already the P^T operand, and V's operand is assembled from
-//      4 row loads per lane, so neither operand goes through LDS.
+//      4 row loads per lane, so neither operand goes through LDS.  Streams that
+//      are longer than equal shares for every workgroup would make them add the
+//      probabilities' bf16 remainders.
 //   5. Merge.  A segment a wave covered whole is normalised and written by that
 //      wave.  The cut pieces (at most 2 per wave) are merged through LDS.  A piece
 //      of a segment that is split across workgroups stores its unnormalised
@@ -69,7 +71,7 @@ namespace rlda {
 namespace {
 
 #ifndef RLDA_MFMA_DEPTH
-#define RLDA_MFMA_DEPTH 3                    // pages in flight per wave, MFMA path
+#define RLDA_MFMA_DEPTH 3                    // pages in registers per wave (one computed, the others in flight), MFMA path
 #endif
 #ifndef RLDA_MFMA_DEPTH_FP8
 #define RLDA_MFMA_DEPTH_FP8 RLDA_MFMA_DEPTH  // ... with fp8 pages (half the bytes each)
@@ -926,14 +928,17 @@ __device__ __forceinline__ StreamChunk fetch_chunk(const Params& p, const int32_
 // rows are written; no cut piece leaves the workgroup.  With one segment there are no
 // boundaries to look for: the ids come 64 at a time ahead of a loop that issues the
 // same loads for every page (past the last one with descriptors of no records), so a
-// wave waits for the page it consumes only and keeps kDepth pages in flight.  What
+// wave waits for the page it consumes only, with kDepth - 1 more in flight.  What
 // bounds it is latency: lengths, ids and the first page are three dependent round trips.
 //   A wave's stream is longer here than under equal shares, and only a stream's largest
 // probability is exact in bf16, so the product takes their remainders as well.  Error
 // against float64, fp32 outputs, 40/8 heads, d = 64, two sequences of 1.1k and 1.2k
-// tokens: equal shares 1.0e-3, whole segments 1.6e-3 without the remainders (11.4 us a
-// call) and 2.4e-6 with them (12.0 us; append + decode of 32 short fp8 sequences 16.7 and
-// 18.5).
+// tokens: equal shares 1.0e-3, whole segments 1.6e-3 without the remainders and 2.4e-6
+// with them.  us a call without / with: 28/4 heads, bf16 d 128, four sequences of 512
+// tokens 9.4 / 9.8; 40/8 d 64, four of 1024 10.3 / 11.4; append + decode of 32 short fp8
+// sequences 16.5 / 18.5.  (Of the 1.1 us at d 64, 0.6 keep an infinite V's infinity;
+// running a stream that ends with a NaN again without remainders instead cost 0.4 us a
+// call in the check alone.)
 template <class Pol>
 __device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int nb, int tail,
                                               float (*sacc)[16][Pol::kD + 4], float (*sml)[16][2]) {
@@ -1022,8 +1027,8 @@ __device__ __forceinline__ void whole_segment(const Params& p, int b, int g, int
 #endif
 constexpr bool kPromptTemporal = RLDA_PROMPT_TEMPORAL;
 
-// The prompt-pass state a grouped run's segment may start from (section 7b of the
-// attention kernel's users): only the launch that follows a prompt pass carries it.
+// The prompt-pass state a grouped run's segment may start from: only the launch that
+// follows a prompt pass carries it.
 struct NoPromptState {};
 template <class Pol, bool PROMPT>
 struct PromptState {
@@ -1629,8 +1634,6 @@ void decode_attention_kernel(const Params p) {
 #pragma unroll
     for (int e = 0; e < DPT; ++e) o[e] = 0.f;
     // Close the group of segment `cur`: write it, or publish this workgroup's piece.
-    // Lane j < 2 kWaves: slot j's segment and its first and last positions, read
-    // for every slot at once (the merge below takes them with readlane).
     // Lane j < 2 kWaves: slot j's segment, its sequence and segment within the
     // sequence, and its first and last positions, read for every slot at once (the
     // merge below takes them with readlane).
