@@ -109,7 +109,12 @@ def work_split(seq_lens: Sequence[int], num_kv_heads: int, ranges: int, head_dim
         over = max(54 - 72 * segs, 26)
     whole = nseg <= ranges and nb - fair <= over
     least = max(min((nb + start_cost) / 16, (1.25 * nb) ** 0.5), 4)
-    shares = int(ranges) if fair >= least else min(int(ranges), nseg * math.ceil(C / (nseg * least)))
+    shares = int(ranges)
+    if fair < least:
+        fewer = nseg * math.ceil(C / (nseg * least))
+        even = C == nseg * (nb + start_cost)   # all segments of one length
+        if fewer < (1.0 if even else 0.7) * ranges:
+            shares = fewer
     return whole, shares
 
 

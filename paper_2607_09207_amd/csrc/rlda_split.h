@@ -73,8 +73,15 @@ struct Split {
 // sqrt(1.25 nbmax), where pages and pieces cost alike (a share's page 0.15 us, a piece
 // 0.19 us).  us a call at d 128, one sequence of 64 / 112 / 188 pages: 8/1 heads bf16
 // 14.4 / - / 16.5 with nbmax / 16 - 1 (18 to 22 pieces) and 13.1 / - / 15.0 so; 12/2 fp8
-// - / 15.1 / - and - / 13.3 / - (12/2 bf16 in 256 shares 31.4).  Where that bound holds the shares are a multiple of the segments, so that equal
-// segments are cut alike.
+// - / 15.1 / - and - / 13.3 / - (12/2 bf16 in 256 shares 31.4).
+//   Fewer shares are a multiple of the segments, so that segments of one length are cut
+// alike.  Segments of unlike lengths are cut anywhere, and little fewer shares save less
+// than the remainders of their longer streams cost, so those keep W unless 0.7 W or fewer
+// do.  us a call with fewer shares less W shares, by shares / W, lengths within a factor of
+// 3, 1 to 24 sequences of 120 to 1300 pages, mean and extremes: bf16 d 128 0.5 -2.5 (-3.5
+// to -1.6), 0.6 -1.1 (-1.5 to -0.3), 0.7 to 0.8 +0.1 (-1.0 to 1.1), above +0.7 (-0.2 to
+// 1.4); fp8 d 128 -2.7 (-3.5 to -0.9), -0.8 (-2.3 to 0.8), -0.1 (-1.6 to 1.8), +1.1 (0.4
+// to 1.7); equal lengths up to W -1.7 (-5.6 to 0.3).
 //   W workgroups (inv_ranges = 1 / W, or 0: the caller fixed the share count), nseg
 // segments costing `cost` together, the largest of nb_max pages.
 RLDA_HD Split split_of(SplitForm form, int W, float inv_ranges, int nseg, int cost, int nb_max) {
@@ -83,12 +90,12 @@ RLDA_HD Split split_of(SplitForm form, int W, float inv_ranges, int nseg, int co
   const float over = form == kSplitGeneral     ? __builtin_fmaxf(46.f - 96.f * segs, 20.f)
                      : form == kSplitFullPages ? __builtin_fmaxf(54.f - 72.f * segs, 26.f)
                                                : (form == kSplitHalfPages64 ? 78.f : 57.f) + __builtin_fmaxf(80.f * segs - 20.f, 0.f);
-  const bool aligned = nseg == W && cost == nseg * (nb_max + kStartCost);
-  Split s = {nseg <= W && nb - fair <= over && !(form == kSplitGeneral && aligned), W};
+  const bool even = cost == (int64_t)nseg * (nb_max + kStartCost);   // all segments of one length
+  Split s = {nseg <= W && nb - fair <= over && !(form == kSplitGeneral && even && nseg == W), W};
   const float least = __builtin_fmaxf(__builtin_fminf(0.0625f * (nb + (float)kStartCost), split_sqrt(1.25f * nb)), 4.f);
   if (fair < least) {
     const float n = (float)nseg * __builtin_ceilf((float)cost * split_rcp((float)nseg * least));
-    s.shares = n < (float)W ? (int)n : W;
+    if (n < (even ? 1.f : 0.7f) * (float)W) s.shares = (int)n;
   }
   return s;
 }

@@ -69,6 +69,21 @@ def test_few_segments_fall_into_one_merge_batch(rule, nseg, nb):
         assert pieces == 1 or (nb + START) / (pieces - 1) >= 4
 
 
+@pytest.mark.parametrize("form", ["full", "half128", "general"])
+def test_unlike_segments_keep_the_workgroups_unless_clearly_fewer_do(rule, form):
+    W = 256
+    for nseg in (4, 12, 41):
+        for nb in (200, 344, 726):
+            for mean in range(20, nb, 7):
+                cost = nseg * (mean + START)
+                s = rule.split(FORMS[form], W, nseg, cost, nb)
+                assert s.shares == W or s.shares <= 0.7 * W, (nseg, nb, mean)
+    # 164 segments of up to 344 pages, 12 of up to 726: 492 of 512 and 216 of 256 shares by the bound on their pages
+    assert rule.split(FORMS["half128"], 512, 164, 9408, 344).shares == 512
+    assert rule.split(FORMS["full"], 256, 12, 6180, 726).shares == 256
+    assert equal(rule, "full", 256, 12, 500).shares == 252   # of one length: cut alike
+
+
 @pytest.mark.parametrize("nb", [1, 64, 112])
 def test_shares_that_are_the_segments_stay_shares_in_the_general_loop(rule, nb):
     """As many segments as workgroups, all of one length: cut nothing, gain nothing."""
